@@ -19,9 +19,8 @@ LIB = os.path.join(HERE, "libzkntt.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["api.cpp", "ntt_kernels.hip", "ntt_batch.hip", "microbench.hip",
-           "ntt_pass_bls_e3.hip", "ntt_pass_bls_e2.hip", "ntt_pass_bls_e1.hip",
-           "ntt_pass_bn_e3.hip", "ntt_pass_bn_e2.hip", "ntt_pass_bn_e1.hip",
-           "ntt_pass_b377_e3.hip", "ntt_pass_b377_e2.hip", "ntt_pass_b377_e1.hip",
+           "ntt_mfma_bls.hip", "ntt_mfma_bn.hip", "ntt_mfma_b377.hip",
+           "ntt_pass_bls.hip", "ntt_pass_bn.hip", "ntt_pass_b377.hip",
            "ntt_pass_bls_f64_e2.hip", "msm.hip"]
 
 ARCH = "gfx950"
@@ -29,6 +28,8 @@ COMMON = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
     # packed FP32 instructions are kept out of every kernel
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the digit matrices (mfma_tables.hpp) are evaluated at compile time
+    "-fconstexpr-steps=100000000",
     "-Wall", "-Wno-unused-function",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]

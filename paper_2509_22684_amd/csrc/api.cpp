@@ -71,7 +71,6 @@ struct ntt_plan {
   int field = 0;
   uint32_t log_n = 0;
   uint64_t n = 0;
-  int log_e = 2;
   uint32_t flags = 0;
   int device = 0;
   std::vector<PassDesc> passes;
@@ -184,19 +183,28 @@ constexpr uint32_t kQuotientForkMaxLog = 22;
 bool quotient_forks(const ntt_plan* p) { return p->log_n <= kQuotientForkMaxLog; }
 
 // Split log_n into passes of at most max_log_r stages each, larger radices
-// first (a single pass covers n up to the tile size in one tile).
-std::vector<int> split_passes(uint32_t log_n, uint32_t max_log_r, uint32_t log_tile) {
+// first (a single pass covers n up to the tile size in one tile).  A column
+// of the FP64 kernels' tiles holds fewer points than the tile; the
+// matrix-core kernels choose their tiles to fit the radix.
+std::vector<int> split_passes(uint32_t log_n, const ntt_plan_opts& o) {
   std::vector<int> r;
-  if (log_n <= log_tile) {
+  if (log_n <= o.log2_tile) {
     r.push_back((int)log_n);
     return r;
   }
-  // a column of a multi-pass tile holds fewer points than the tile
-  max_log_r = std::min(max_log_r, log_tile - 1);
+  uint32_t max_log_r = o.log2_pass_radix;
+  if (o.flags & ZK_FLAG_FFMUL_FP64) max_log_r = std::min(max_log_r, o.log2_tile - 1);
   const int P = (int)((log_n + max_log_r - 1) / max_log_r);
   const int base = (int)log_n / P, extra = (int)log_n % P;
   for (int k = 0; k < P; ++k) r.push_back(base + (k < extra ? 1 : 0));
   return r;
+}
+
+// A kernel exists for a radix-2^log_r pass of this schedule.
+bool pass_supported(uint32_t log_n, const ntt_plan_opts& o, int log_r) {
+  if (o.flags & ZK_FLAG_FFMUL_FP64)
+    return zk::fp64_shape_supported(log_r, (int)std::min(log_n, o.log2_tile));
+  return ((uint32_t)log_r == log_n && log_r <= zk::kTinyLog) || zk::mfma_supported(log_r, log_n);
 }
 
 template <class F>
@@ -224,7 +232,7 @@ int build_plan(ntt_plan* p) {
     p->zinv = zk::inv_mont<F>(zk::sub<F>(gn, one));
   }
 
-  std::vector<int> radices = split_passes(L, p->max_log_r, p->log_tile);
+  std::vector<int> radices = split_passes(L, p->opts);
   uint32_t log_ns = 0;
   Fe* tw_r_by_log[33] = {nullptr};
   for (size_t k = 0; k < radices.size(); ++k) {
@@ -232,7 +240,7 @@ int build_plan(ntt_plan* p) {
     d.log_r = radices[k];
     d.log_tile = (L <= p->log_tile) ? (int)L : (int)p->log_tile;
     d.log_ns = log_ns;
-    if (!zk::pass_shape_supported(d.log_r, d.log_tile, p->log_e))
+    if (!pass_supported(L, p->opts, d.log_r))
       return fail(ZK_EUNSUPPORTED, "no pass kernel for a radix-2^" + std::to_string(d.log_r) +
                                        " pass; choose a larger log2_pass_radix");
     if (!tw_r_by_log[d.log_r]) {
@@ -469,7 +477,7 @@ int run_transform(const ntt_plan* p, Kind kind, const void* in, void* out, void*
     }
     const PassDesc& d = p->passes[k];
     const zk::PassArgs a = make_pass_args(p, kind, k, in, out, work);
-    hipError_t e = zk::launch_pass(p->kfield, d.log_r, d.log_tile, p->log_e, a, s);
+    hipError_t e = zk::launch_pass(p->kfield, d.log_r, d.log_tile, a, s);
     if (e != hipSuccess) return hip_fail(e, "NTT pass launch");
   }
   if (events) {
@@ -495,7 +503,7 @@ int run_forward_pointwise(const ntt_plan* p, const void* in, void* out, void* wo
       args.pw_b = b;
       args.post_const = p->zinv;
     }
-    hipError_t e = zk::launch_pass(p->field, d.log_r, d.log_tile, p->log_e, args, s);
+    hipError_t e = zk::launch_pass(p->field, d.log_r, d.log_tile, args, s);
     if (e != hipSuccess) return hip_fail(e, "NTT pass launch");
   }
   return ZK_OK;
@@ -574,7 +582,6 @@ int ntt_plan_create(ntt_plan** out, int field, uint32_t log2n, const ntt_plan_op
   p->field = field;
   p->log_n = log2n;
   p->n = 1ull << log2n;
-  p->log_e = (int)o.log2_radix;
   p->flags = o.flags;
   p->twiddle_mode = o.twiddle_mode;
   p->max_log_r = o.log2_pass_radix;
@@ -639,13 +646,12 @@ size_t ntt_plan_table_bytes(int field, uint32_t log2n, const ntt_plan_opts* opts
   ntt_plan_opts o{};
   if (resolve_opts(field, log2n, opts, &o) != ZK_OK) return 0;
   // the allocations build_plan makes for this schedule
-  const std::vector<int> radices = split_passes(log2n, o.log2_pass_radix, o.log2_tile);
-  const int log_tile = log2n <= o.log2_tile ? (int)log2n : (int)o.log2_tile;
+  const std::vector<int> radices = split_passes(log2n, o);
   uint64_t elems = 0;
   bool seen[33] = {false};
   uint32_t log_ns = 0;
   for (size_t k = 0; k < radices.size(); ++k) {
-    if (!zk::pass_shape_supported(radices[k], log_tile, (int)o.log2_radix)) {
+    if (!pass_supported(log2n, o, radices[k])) {
       fail(ZK_EUNSUPPORTED, "no pass kernel for a radix-2^" + std::to_string(radices[k]) + " pass");
       return 0;
     }
@@ -1119,7 +1125,7 @@ int batch_enqueue(const ntt_batch* b, hipStream_t s) {
     }
     for (size_t q = 0; q < d.pass.size() && rc == ZK_OK; ++q) {
       const PassDesc& pd = d.plan->passes[q];
-      e = zk::launch_pass(d.plan->field, pd.log_r, pd.log_tile, 2, d.pass[q], ds);
+      e = zk::launch_pass(d.plan->field, pd.log_r, pd.log_tile, d.pass[q], ds);
       if (e != hipSuccess) rc = hip_fail(e, "grouped pass launch");
     }
   }

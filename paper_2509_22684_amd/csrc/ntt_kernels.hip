@@ -1,7 +1,7 @@
 // Auxiliary kernels (table generation, pointwise quotient, validation) and
 // the pass dispatcher.  The pass kernels themselves are instantiated per
-// field and in-register radix in ntt_pass_<field>_e<k>.hip so they compile in
-// parallel.
+// field in ntt_mfma_<field>.hip, ntt_pass_<field>.hip (tiny transforms) and
+// ntt_pass_bls_f64_e2.hip so they compile in parallel.
 #include <algorithm>
 
 #include "field_f64.hpp"
@@ -10,16 +10,13 @@
 
 namespace zk {
 
-hipError_t launch_pass_bls_e3(int log_r, int log_tile, const PassArgs& a, hipStream_t s);
-hipError_t launch_pass_bls_e2(int log_r, int log_tile, const PassArgs& a, hipStream_t s);
-hipError_t launch_pass_bls_e1(int log_r, int log_tile, const PassArgs& a, hipStream_t s);
-hipError_t launch_pass_bn_e3(int log_r, int log_tile, const PassArgs& a, hipStream_t s);
-hipError_t launch_pass_bn_e2(int log_r, int log_tile, const PassArgs& a, hipStream_t s);
-hipError_t launch_pass_bn_e1(int log_r, int log_tile, const PassArgs& a, hipStream_t s);
-hipError_t launch_pass_b377_e3(int log_r, int log_tile, const PassArgs& a, hipStream_t s);
-hipError_t launch_pass_b377_e2(int log_r, int log_tile, const PassArgs& a, hipStream_t s);
-hipError_t launch_pass_b377_e1(int log_r, int log_tile, const PassArgs& a, hipStream_t s);
+hipError_t launch_pass_bls(int log_r, const PassArgs& a, hipStream_t s);
+hipError_t launch_pass_bn(int log_r, const PassArgs& a, hipStream_t s);
+hipError_t launch_pass_b377(int log_r, const PassArgs& a, hipStream_t s);
 hipError_t launch_pass_bls_f64_e2(int log_r, int log_tile, const PassArgs& a, hipStream_t s);
+hipError_t launch_mfma_bls(int log_r, const PassArgs& a, hipStream_t s);
+hipError_t launch_mfma_bn(int log_r, const PassArgs& a, hipStream_t s);
+hipError_t launch_mfma_b377(int log_r, const PassArgs& a, hipStream_t s);
 
 namespace {
 using detail::load_fe;
@@ -85,22 +82,13 @@ inline uint32_t blocks_for(uint64_t n, uint32_t per) { return (uint32_t)((n + pe
 
 }  // namespace
 
-hipError_t launch_pass(int field, int log_r, int log_tile, int log_e, const PassArgs& a, hipStream_t s) {
-  if (field == Bls12_381Fr::ID) {
-    if (log_e == 3) return launch_pass_bls_e3(log_r, log_tile, a, s);
-    if (log_e == 2) return launch_pass_bls_e2(log_r, log_tile, a, s);
-    if (log_e == 1) return launch_pass_bls_e1(log_r, log_tile, a, s);
-  } else if (field == Bn254Fr::ID) {
-    if (log_e == 3) return launch_pass_bn_e3(log_r, log_tile, a, s);
-    if (log_e == 2) return launch_pass_bn_e2(log_r, log_tile, a, s);
-    if (log_e == 1) return launch_pass_bn_e1(log_r, log_tile, a, s);
-  } else if (field == Bls12_377Fr::ID) {
-    if (log_e == 3) return launch_pass_b377_e3(log_r, log_tile, a, s);
-    if (log_e == 2) return launch_pass_b377_e2(log_r, log_tile, a, s);
-    if (log_e == 1) return launch_pass_b377_e1(log_r, log_tile, a, s);
-  } else if (field == kFieldBls12_381Fp64) {
-    if (log_e == 2) return launch_pass_bls_f64_e2(log_r, log_tile, a, s);
-  }
+hipError_t launch_pass(int field, int log_r, int log_tile, const PassArgs& a, hipStream_t s) {
+  if (field == kFieldBls12_381Fp64) return launch_pass_bls_f64_e2(log_r, log_tile, a, s);
+  const bool tiny = (uint32_t)log_r == a.log_n && log_r <= kTinyLog;
+  if (!tiny && !mfma_supported(log_r, a.log_n)) return hipErrorInvalidValue;
+  if (field == Bls12_381Fr::ID) return tiny ? launch_pass_bls(log_r, a, s) : launch_mfma_bls(log_r, a, s);
+  if (field == Bn254Fr::ID) return tiny ? launch_pass_bn(log_r, a, s) : launch_mfma_bn(log_r, a, s);
+  if (field == Bls12_377Fr::ID) return tiny ? launch_pass_b377(log_r, a, s) : launch_mfma_b377(log_r, a, s);
   return hipErrorInvalidValue;
 }
 

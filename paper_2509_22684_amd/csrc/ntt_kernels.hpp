@@ -52,14 +52,24 @@ struct PassArgs {
   uint32_t log_grp_tiles;
 };
 
-// Shapes the pass kernels are instantiated for: tiles of 2^10 or 2^11
-// elements with 2^3 .. 2^9 points per column, tiles of 2^8 elements with
-// 2^3 .. 2^7 points per column (two or four elements per thread only), or
-// one tile holding a whole transform of up to 2^11 points.
-inline bool pass_shape_supported(int log_r, int log_tile, int log_e = 2) {
+// Transforms of at most 2^kTinyLog points run in one workgroup of the
+// register kernels (ntt_pass_impl.hpp).
+constexpr int kTinyLog = 7;
+
+// Passes the matrix-core kernels run (ntt_mfma_impl.hpp): radix 2^3 .. 2^9
+// of a multi-pass transform, and whole transforms of 2^8 to 2^11 points.
+inline bool mfma_supported(int log_r, uint32_t log_n) {
+  return (uint32_t)log_r == log_n ? log_r > kTinyLog && log_r <= 11 : log_n > 8 && log_r >= 3 && log_r <= 9;
+}
+
+// Shapes the FP64 product's register kernels are instantiated for: tiles of
+// 2^10 or 2^11 elements with 2^3 .. 2^9 points per column, tiles of 2^8
+// elements with 2^3 .. 2^7 points per column, or one tile holding a whole
+// transform of up to 2^11 points.
+inline bool fp64_shape_supported(int log_r, int log_tile) {
   if (log_tile == 11) return (log_r >= 3 && log_r <= 9) || log_r == 11;
   if (log_tile == 10 && log_r >= 3 && log_r <= 9) return true;
-  if (log_tile == 8 && log_r >= 3 && log_r <= 7 && log_e <= 2) return true;
+  if (log_tile == 8 && log_r >= 3 && log_r <= 7) return true;
   return log_tile == log_r && log_r >= 0 && log_r <= 10;
 }
 
@@ -71,9 +81,11 @@ constexpr int kFieldBls12_381Fp64 = 101;
 // a_i b_i 2^-288 mod p (variant 1, the FP64 product), for i < n.
 hipError_t launch_field_mul(int field, int variant, const Fe* a, const Fe* b, Fe* out, uint64_t n, hipStream_t s);
 
-// Launch one pass; log_r + log_j = log_tile.  Returns hipSuccess or the
-// launch error.
-hipError_t launch_pass(int field, int log_r, int log_tile, int log_e, const PassArgs& a, hipStream_t s);
+// Launch one radix-2^log_r pass.  log_tile (elements per workgroup) is used
+// by the FP64 product's kernels; the others choose their tile from the number
+// of elements in the launch and set log_grp_tiles to match.  Returns
+// hipSuccess or the launch error.
+hipError_t launch_pass(int field, int log_r, int log_tile, const PassArgs& a, hipStream_t s);
 
 // Table generation: out[t] = scale * base^e(t) for t < count, with
 // e(t) = t (kGenPowers) or e(t) = mult * (t / ns) * (t mod ns) (kGenPassTwiddle).

@@ -1,0 +1,8 @@
+// Whole transforms of at most 2^7 points over BLS12-377 Fr.
+#include "ntt_pass_impl.hpp"
+
+namespace zk {
+hipError_t launch_pass_b377(int log_r, const PassArgs& a, hipStream_t s) {
+  return detail::dispatch_tiny<Bls12_377Fr>(log_r, a, s);
+}
+}  // namespace zk

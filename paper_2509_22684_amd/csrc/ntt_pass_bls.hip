@@ -1,0 +1,8 @@
+// Whole transforms of at most 2^7 points over BLS12-381 Fr.
+#include "ntt_pass_impl.hpp"
+
+namespace zk {
+hipError_t launch_pass_bls(int log_r, const PassArgs& a, hipStream_t s) {
+  return detail::dispatch_tiny<Bls12_381Fr>(log_r, a, s);
+}
+}  // namespace zk

@@ -430,30 +430,29 @@ namespace zk {
 namespace detail {
 
 template <class F, int LOG_R, int LOG_TILE, int LOG_E>
-hipError_t launch_one(const PassArgs& a, hipStream_t s) {
+hipError_t launch_one(const PassArgs& a0, hipStream_t s) {
   using S = PassShape<LOG_R, LOG_TILE, LOG_E>;
+  PassArgs a = a0;
+  a.log_grp_tiles = a.log_n - LOG_TILE;
   const uint64_t tiles = ((1ull << a.log_n) >> LOG_TILE) * (a.grp_jobs ? a.grp_jobs : 1u);
   hipLaunchKernelGGL((ntt_pass_kernel<F, LOG_R, LOG_TILE, LOG_E>), dim3((uint32_t)tiles), dim3(S::THREADS), 0, s, a);
   return hipGetLastError();
 }
 
-// Multi-pass tiles of 2^11 or 2^10 elements with radix 2^3 .. 2^9 per pass,
-// 2^8-element tiles with radix 2^3 .. 2^8 for two or four elements per
-// thread (small transforms spread over more CUs), and single-pass transforms
-// of up to 2^11 points held in one tile.  Keep in step with
-// pass_shape_supported().
+// FP64 product: multi-pass tiles of 2^11 or 2^10 elements with radix
+// 2^3 .. 2^9 per pass, 2^8-element tiles with radix 2^3 .. 2^7, and
+// single-pass transforms of up to 2^11 points held in one tile.  Keep in step
+// with fp64_shape_supported().
 template <class F, int LOG_E>
 hipError_t dispatch_shape(int log_r, int log_tile, const PassArgs& a, hipStream_t s) {
-  if constexpr (LOG_E <= 2) {
-    if (log_tile == 8 && log_r < 8) {
-      switch (log_r) {
-        case 3: return launch_one<F, 3, 8, LOG_E>(a, s);
-        case 4: return launch_one<F, 4, 8, LOG_E>(a, s);
-        case 5: return launch_one<F, 5, 8, LOG_E>(a, s);
-        case 6: return launch_one<F, 6, 8, LOG_E>(a, s);
-        case 7: return launch_one<F, 7, 8, LOG_E>(a, s);
-        default: break;
-      }
+  if (log_tile == 8 && log_r < 8) {
+    switch (log_r) {
+      case 3: return launch_one<F, 3, 8, LOG_E>(a, s);
+      case 4: return launch_one<F, 4, 8, LOG_E>(a, s);
+      case 5: return launch_one<F, 5, 8, LOG_E>(a, s);
+      case 6: return launch_one<F, 6, 8, LOG_E>(a, s);
+      case 7: return launch_one<F, 7, 8, LOG_E>(a, s);
+      default: break;
     }
   }
   if (log_tile == 10 && log_r < 10) {
@@ -498,6 +497,23 @@ hipError_t dispatch_shape(int log_r, int log_tile, const PassArgs& a, hipStream_
     }
   }
   return hipErrorInvalidValue;
+}
+
+// Whole transforms of at most 2^kTinyLog points, radix-2 rounds (a lone
+// workgroup: more threads per tile shorten it).
+template <class F>
+hipError_t dispatch_tiny(int log_r, const PassArgs& a, hipStream_t s) {
+  switch (log_r) {
+    case 0: return launch_one<F, 0, 0, 1>(a, s);
+    case 1: return launch_one<F, 1, 1, 1>(a, s);
+    case 2: return launch_one<F, 2, 2, 1>(a, s);
+    case 3: return launch_one<F, 3, 3, 1>(a, s);
+    case 4: return launch_one<F, 4, 4, 1>(a, s);
+    case 5: return launch_one<F, 5, 5, 1>(a, s);
+    case 6: return launch_one<F, 6, 6, 1>(a, s);
+    case 7: return launch_one<F, 7, 7, 1>(a, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace detail
