@@ -1682,7 +1682,7 @@ struct msm_bases {
   uint32_t per_group = 1;  // scalars per histogram group
   uint32_t groups = 1;
   uint32_t lanes = 1;      // accumulation lanes
-  uint32_t kmin = 32;      // fewest sorted entries per accumulation lane
+  uint32_t kmin = 8;       // fewest sorted entries per accumulation lane
   void* table = nullptr;
 };
 
@@ -1691,8 +1691,8 @@ namespace {
 constexpr int kScalarBits = 255;  // BLS12-381 Fr elements are below 2^255
 
 struct MsmLayout {
-  size_t digits, ranks, hist, counts, offsets, entries, head, tail, big, big_count, buckets, chunk_sums, level_a,
-      level_b, total;
+  size_t digits, ranks, hist, counts, offsets, entries, head, tail, big_count, big_bucket, big_item, big_part, buckets,
+      level_a, level_b, total;
 };
 
 size_t round256(size_t b) { return (b + 255) / 256 * 256; }
@@ -1701,10 +1701,8 @@ MsmLayout msm_layout(const msm_bases* b) {
   MsmLayout L{};
   const size_t nb = size_t(1) << b->c;
   const size_t entries = (size_t)b->windows * b->n;
-  const size_t T = (nb + zk::msm::kChunk - 1) / zk::msm::kChunk;
-  const size_t per = (size_t)zk::msm::kLevel0Lanes * zk::msm::kLevel0Chunks;
-  const size_t T0 = (T + per - 1) / per;
-  const size_t xyzz = zk::msm::kXyzzWords * sizeof(uint32_t);
+  const int low = std::min(b->c, zk::msm::kTreeLevels);
+  const size_t point = zk::msm::kAccWords * sizeof(uint32_t);
   size_t off = 0;
   L.digits = off;
   off += round256(entries * sizeof(uint16_t));
@@ -1719,21 +1717,23 @@ MsmLayout msm_layout(const msm_bases* b) {
   L.entries = off;
   off += round256(entries * sizeof(uint32_t));
   L.head = off;
-  off += round256((size_t)b->lanes * xyzz);
+  off += round256((size_t)b->lanes * point);
   L.tail = off;
-  off += round256((size_t)b->lanes * xyzz);
-  L.big = off;
-  off += round256((size_t)zk::msm::max_big_buckets(b->lanes) * sizeof(uint32_t));
+  off += round256((size_t)b->lanes * point);
   L.big_count = off;
-  off += round256(sizeof(uint32_t));
+  off += round256(2 * sizeof(uint32_t));
+  L.big_bucket = off;
+  off += round256((size_t)zk::msm::max_big_buckets(b->lanes) * sizeof(uint4));
+  L.big_item = off;
+  off += round256((size_t)zk::msm::max_big_items(b->lanes) * sizeof(uint32_t));
+  L.big_part = off;
+  off += round256((size_t)zk::msm::max_big_items(b->lanes) * point);
   L.buckets = off;
-  off += round256(nb * xyzz);
-  L.chunk_sums = off;
-  off += round256(T * xyzz);
+  off += round256(nb * point);
   L.level_a = off;
-  off += round256((size_t)b->c * T0 * xyzz);
+  off += round256(((size_t)(1 + low) << (b->c - low)) * point);
   L.level_b = off;
-  off += round256((size_t)b->c * xyzz);
+  off += round256((size_t)b->c * point);
   L.total = off;
   return L;
 }
@@ -1770,6 +1770,11 @@ int msm_bases_create(msm_bases** out, const void* d_points, uint64_t n, uint32_t
   // group below 2^16
   b->per_group = (uint32_t)std::min<uint64_t>(n, 65535u / (uint32_t)windows);
   b->groups = (uint32_t)((n + b->per_group - 1) / b->per_group);
+  // Fewest entries per lane: a mixed addition in a lane takes about twice as
+  // long as the addition of a run's head by a quad, so runs of about an eighth
+  // of a bucket, and no fewer than eight entries, end soonest when there are
+  // lanes to spare.
+  b->kmin = (uint32_t)std::max<uint64_t>(8, ((uint64_t)windows * n) >> (c + 3));
   // accumulation lanes: the resident ones, fewer when the entries are few
   e = zk::msm::accumulate_lanes(&b->lanes);
   if (e != hipSuccess) {
@@ -1787,7 +1792,7 @@ int msm_bases_create(msm_bases** out, const void* d_points, uint64_t n, uint32_t
   // the precomputation's XYZZ scratch, a chunk of points at a time
   const uint64_t chunk_pts = std::min<uint64_t>(n, 1ull << 18);
   void* scratch = nullptr;
-  e = hipMalloc(&scratch, (size_t)chunk_pts * windows * 60 * sizeof(uint32_t));
+  e = hipMalloc(&scratch, (size_t)chunk_pts * windows * zk::msm::kScratchWords * sizeof(uint32_t));
   hipStream_t s = static_cast<hipStream_t>(stream);
   const uint32_t* pts = static_cast<const uint32_t*>(d_points);
   uint32_t* table = static_cast<uint32_t*>(b->table);
@@ -1856,10 +1861,11 @@ int msm_compute(const msm_bases* b, const void* d_scalars, void* d_result, void*
   m.entries = reinterpret_cast<uint32_t*>(w + L.entries);
   m.head = reinterpret_cast<uint32_t*>(w + L.head);
   m.tail = reinterpret_cast<uint32_t*>(w + L.tail);
-  m.big = reinterpret_cast<uint32_t*>(w + L.big);
-  m.big_count = reinterpret_cast<uint32_t*>(w + L.big_count);
+  m.big.count = reinterpret_cast<uint32_t*>(w + L.big_count);
+  m.big.bucket = reinterpret_cast<uint4*>(w + L.big_bucket);
+  m.big.item = reinterpret_cast<uint32_t*>(w + L.big_item);
+  m.big.part = reinterpret_cast<uint32_t*>(w + L.big_part);
   m.buckets = reinterpret_cast<uint32_t*>(w + L.buckets);
-  m.chunk_sums = reinterpret_cast<uint32_t*>(w + L.chunk_sums);
   m.level_a = reinterpret_cast<uint32_t*>(w + L.level_a);
   m.level_b = reinterpret_cast<uint32_t*>(w + L.level_b);
   m.result = static_cast<uint32_t*>(d_result);

@@ -1,17 +1,21 @@
-// The base field of BLS12-381 G1, F_q (381-bit q), for the MSM kernels.
+// The base field of BLS12-381 G1, F_q (381-bit q), for the MSM kernels, on
+// fourteen signed limbs of 28 bits.
 //
-// An element is twelve 32-bit limbs, little-endian, in Montgomery form with
-// R = 2^384.  Inside the kernels elements are kept in [0, 2q) (lazy
-// reduction: 4q < 2^384, so a Montgomery product of two such elements is
-// below 2q without a final subtraction, and sums and differences reduce
-// modulo 2q); canon() brings one to [0, q) where it leaves the device.
-// FF_mul is the same finely integrated product scanning as the scalar
-// fields' (field.hpp): each 32x32-bit partial product is one v_mad_u64_u32
-// into a 64-bit column accumulator whose carry-out feeds a v_addc_co_u32
-// column counter, 2 N^2 = 288 of each per product; K independent products
-// (mul2, mul3, mul4) interleave column by column, each chain keeping its own
-// carry SGPR pair.  FF_add / FF_sub are branchless carry chains with a
-// borrow-select.
+// In 32-bit limbs every partial product of a Montgomery product is two
+// instructions: the multiply-add and the add of its carry into the column's
+// counter (300 and 288 of them at twelve limbs).  With 28-bit limbs the 28
+// products of a column fit a signed 64-bit accumulator with room for operands
+// a few bits above 28, so there are no carry counts, sums and differences
+// are fourteen independent 32-bit adds with no reduction, and two products
+// can share one reduction.  A product is 392 multiply-adds (301 for a square)
+// and about 80 shifts and masks.
+//
+// A value is sum_i v_i 2^(28 i), congruent to the element it stands for times
+// 2^392 (Montgomery form).  Products are (a b - m q) / 2^392 with
+// 0 <= m < 2^392, so for |a b| < 2^9 q^2 they lie in (-1.2 q, 0.2 q)
+// (q = 2^380.7), and come out normalised: limbs 0 .. 12 in [0, 2^28), the
+// sign in limb 13.  Operand limbs may reach 2^28 + 2^30 in one factor with the
+// other normalised, or 2^29 in both: columns then stay below 2^62.8.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>
@@ -19,211 +23,252 @@
 namespace zk {
 namespace fq {
 
-constexpr int kN = 12;
+constexpr int kN = 14;       // limbs
+constexpr int kBits = 28;
+constexpr uint32_t kMask = (1u << kBits) - 1;
+constexpr int kWords = 12;   // 32-bit words of a packed element
 
 // q = (x0 - 1)^2 (x0^4 - x0^2 + 1) / 3 + x0, x0 = -0xd201000000010000.
-constexpr uint32_t kQ[kN] = {0xffffaaabu, 0xb9feffffu, 0xb153ffffu, 0x1eabfffeu, 0xf6b0f624u, 0x6730d2a0u,
-                             0xf38512bfu, 0x64774b84u, 0x434bacd7u, 0x4b1ba7b6u, 0x397fe69au, 0x1a0111eau};
-constexpr uint32_t k2Q[kN] = {0xffff5556u, 0x73fdffffu, 0x62a7ffffu, 0x3d57fffdu, 0xed61ec48u, 0xce61a541u,
-                              0xe70a257eu, 0xc8ee9709u, 0x869759aeu, 0x96374f6cu, 0x72ffcd34u, 0x340223d4u};
-constexpr uint32_t kInv = 0xfffcfffdu;  // -q^-1 mod 2^32
-// 2^384 mod q: the Montgomery form of 1.
-constexpr uint32_t kOne[kN] = {0x0002fffdu, 0x76090000u, 0xc40c0002u, 0xebf4000bu, 0x53c758bau, 0x5f489857u,
-                               0x70525745u, 0x77ce5853u, 0xa256ec6du, 0x5c071a97u, 0xfa80e493u, 0x15f65ec3u};
+struct Words {
+  uint32_t v[kWords];
+};
+constexpr Words kQ = {{0xffffaaabu, 0xb9feffffu, 0xb153ffffu, 0x1eabfffeu, 0xf6b0f624u, 0x6730d2a0u, 0xf38512bfu,
+                       0x64774b84u, 0x434bacd7u, 0x4b1ba7b6u, 0x397fe69au, 0x1a0111eau}};
 
-struct __align__(16) Fq {
-  uint32_t v[kN];
+constexpr Words pow2_mod_q(int e) {  // 2^e mod q
+  Words x{};
+  x.v[0] = 1;
+  for (int s = 0; s < e; ++s) {
+    uint32_t c = 0;
+    for (int i = 0; i < kWords; ++i) {
+      const uint32_t hi = x.v[i] >> 31;
+      x.v[i] = (x.v[i] << 1) | c;
+      c = hi;
+    }
+    bool ge = true;
+    for (int i = kWords - 1; i >= 0; --i)
+      if (x.v[i] != kQ.v[i]) {
+        ge = x.v[i] > kQ.v[i];
+        break;
+      }
+    if (!ge) continue;
+    uint64_t br = 0;
+    for (int i = 0; i < kWords; ++i) {
+      const uint64_t d = (uint64_t)x.v[i] - kQ.v[i] - br;
+      x.v[i] = (uint32_t)d;
+      br = (d >> 32) & 1u;
+    }
+  }
+  return x;
+}
+
+constexpr int32_t limb(const Words& w, int i) {
+  uint32_t r = 0;
+  for (int b = 0; b < kBits; ++b) {
+    const int bit = kBits * i + b;
+    if (bit < 32 * kWords) r |= ((w.v[bit / 32] >> (bit % 32)) & 1u) << b;
+  }
+  return (int32_t)r;
+}
+
+struct Limbs {
+  int32_t v[kN];
+};
+constexpr Limbs limbs_of(const Words& w) {
+  Limbs r{};
+  for (int i = 0; i < kN; ++i) r.v[i] = limb(w, i);
+  return r;
+}
+
+constexpr Limbs kQ28 = limbs_of(kQ);
+constexpr uint32_t inv_mod_2_28(uint32_t a) {  // a^-1 mod 2^28, Newton
+  uint32_t x = a;
+  for (int i = 0; i < 5; ++i) x *= 2u - a * x;
+  return x & kMask;
+}
+constexpr uint32_t kInv = inv_mod_2_28(kQ.v[0]);
+constexpr Limbs kOne = limbs_of(pow2_mod_q(392));    // Montgomery form of 1
+constexpr Limbs kTo392 = limbs_of(pow2_mod_q(400));  // times this: form 2^384 -> form 2^392
+constexpr Limbs kTo384 = limbs_of(pow2_mod_q(384));  // times this: form 2^392 -> form 2^384
+
+struct Fq {
+  int32_t v[kN];
 };
 
-__device__ __forceinline__ Fq zero() {
+__device__ __forceinline__ Fq constant(const Limbs& c) {
   Fq r;
 #pragma unroll
-  for (int j = 0; j < kN; ++j) r.v[j] = 0;
+  for (int i = 0; i < kN; ++i) r.v[i] = c.v[i];
   return r;
 }
+__device__ __forceinline__ Fq zero() { return constant(Limbs{}); }
+__device__ __forceinline__ Fq one() { return constant(kOne); }
 
-__device__ __forceinline__ Fq one() {
-  Fq r;
-#pragma unroll
-  for (int j = 0; j < kN; ++j) r.v[j] = kOne[j];
-  return r;
-}
-
-// a = 0 mod q, for a in [0, 2q): a is 0 or q.
-__device__ __forceinline__ bool is_zero(const Fq& a) {
-  uint32_t o = 0, oq = 0;
-#pragma unroll
-  for (int j = 0; j < kN; ++j) {
-    o |= a.v[j];
-    oq |= a.v[j] ^ kQ[j];
-  }
-  return o == 0 || oq == 0;
-}
-
-// a in [0, 2q) to [0, q).
-__device__ __forceinline__ Fq canon(const Fq& a) {
-  Fq d;
-  unsigned int br = 0;
-#pragma unroll
-  for (int j = 0; j < kN; ++j) d.v[j] = __builtin_subc(a.v[j], kQ[j], br, &br);
-#pragma unroll
-  for (int j = 0; j < kN; ++j) d.v[j] = br ? a.v[j] : d.v[j];
-  return d;
-}
-
-// a + b mod 2q (a, b in [0, 2q); a + b < 4q < 2^384).
+// Limb by limb, no carries.
 __device__ __forceinline__ Fq add(const Fq& a, const Fq& b) {
-  Fq s, d;
-  unsigned int c = 0, br = 0;
+  Fq r;
 #pragma unroll
-  for (int j = 0; j < kN; ++j) s.v[j] = __builtin_addc(a.v[j], b.v[j], c, &c);
-#pragma unroll
-  for (int j = 0; j < kN; ++j) d.v[j] = __builtin_subc(s.v[j], k2Q[j], br, &br);
-#pragma unroll
-  for (int j = 0; j < kN; ++j) d.v[j] = br ? s.v[j] : d.v[j];
-  return d;
+  for (int i = 0; i < kN; ++i) r.v[i] = a.v[i] + b.v[i];
+  return r;
 }
-
-// a - b mod 2q (a, b in [0, 2q)).
 __device__ __forceinline__ Fq sub(const Fq& a, const Fq& b) {
-  Fq d;
-  unsigned int br = 0, c = 0;
+  Fq r;
 #pragma unroll
-  for (int j = 0; j < kN; ++j) d.v[j] = __builtin_subc(a.v[j], b.v[j], br, &br);
-  const uint32_t mask = 0u - br;
-#pragma unroll
-  for (int j = 0; j < kN; ++j) d.v[j] = __builtin_addc(d.v[j], k2Q[j] & mask, c, &c);
-  return d;
+  for (int i = 0; i < kN; ++i) r.v[i] = a.v[i] - b.v[i];
+  return r;
 }
-
+__device__ __forceinline__ Fq neg(const Fq& a) {
+  Fq r;
+#pragma unroll
+  for (int i = 0; i < kN; ++i) r.v[i] = -a.v[i];
+  return r;
+}
 __device__ __forceinline__ Fq dbl(const Fq& a) { return add(a, a); }
 
-#if defined(__HIP_DEVICE_COMPILE__)
-__device__ __forceinline__ uint64_t mad_vv(uint32_t a, uint32_t b, uint64_t c, uint64_t& co) {
-  uint64_t r;
-  asm volatile("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(r), "+s"(co) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-__device__ __forceinline__ uint64_t mad_vs(uint32_t a, uint32_t b, uint64_t c, uint64_t& co) {
-  uint64_t r;
-  asm volatile("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(r), "+s"(co) : "v"(a), "s"(b), "v"(c));
-  return r;
-}
-__device__ __forceinline__ uint32_t addc(uint32_t x, uint64_t& co) {
-  uint32_t r;
-  asm volatile("v_addc_co_u32_e64 %0, %1, %2, 0, %1" : "=v"(r), "+s"(co) : "v"(x));
-  return r;
-}
-
-// K independent Montgomery products r[k] = a[k] b[k] 2^-384 mod q, column by
-// column in lock step (see the file comment).
-template <int K>
-__device__ __forceinline__ void mul_k(Fq* r, const Fq* a, const Fq* b) {
-  uint32_t m[K][kN], t[K][kN];
-  uint64_t acc[K], co[K];
-  uint32_t hi[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    acc[k] = 0;
-    hi[k] = 0;
-    co[k] = 0;
-  }
-#define ZK_FQ_TERMS(X, Y, MADFN)                                                  \
-  {                                                                               \
-    _Pragma("unroll") for (int k = 0; k < K; ++k) acc[k] = MADFN(X, Y, acc[k], co[k]); \
-    _Pragma("unroll") for (int k = 0; k < K; ++k) hi[k] = addc(hi[k], co[k]);     \
-  }
+// Limbs 0 .. 12 back to [0, 2^28).
+__device__ __forceinline__ Fq normalise(const Fq& a) {
+  Fq r;
+  int32_t c = 0;
 #pragma unroll
   for (int i = 0; i < kN; ++i) {
-#pragma unroll
-    for (int j = 0; j < i; ++j) {
-      ZK_FQ_TERMS(a[k].v[j], b[k].v[i - j], mad_vv);
-      ZK_FQ_TERMS(m[k][j], kQ[i - j], mad_vs);
-    }
-    ZK_FQ_TERMS(a[k].v[i], b[k].v[0], mad_vv);
-#pragma unroll
-    for (int k = 0; k < K; ++k) m[k][i] = (uint32_t)acc[k] * kInv;
-    ZK_FQ_TERMS(m[k][i], kQ[0], mad_vs);
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      acc[k] = (acc[k] >> 32) | ((uint64_t)hi[k] << 32);
-      hi[k] = 0;
-    }
+    const int32_t x = a.v[i] + c;
+    r.v[i] = i + 1 < kN ? (int32_t)((uint32_t)x & kMask) : x;
+    c = x >> kBits;
   }
-#pragma unroll
-  for (int i = kN; i < 2 * kN; ++i) {
-#pragma unroll
-    for (int j = i - (kN - 1); j < kN; ++j) {
-      ZK_FQ_TERMS(a[k].v[j], b[k].v[i - j], mad_vv);
-      ZK_FQ_TERMS(m[k][j], kQ[i - j], mad_vs);
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      t[k][i - kN] = (uint32_t)acc[k];
-      acc[k] = (acc[k] >> 32) | ((uint64_t)hi[k] << 32);
-      hi[k] = 0;
-    }
-  }
-#undef ZK_FQ_TERMS
-  // t < 2q for a, b < 2q: left there (lazy reduction)
-#pragma unroll
-  for (int k = 0; k < K; ++k)
-#pragma unroll
-    for (int j = 0; j < kN; ++j) r[k].v[j] = t[k][j];
-}
-#else
-// Host compilation pass: device code is parsed but never emitted here.
-template <int K>
-__device__ inline void mul_k(Fq* r, const Fq* a, const Fq* b) {
-  for (int k = 0; k < K; ++k) r[k] = a[k];
-  (void)b;
-}
-#endif
-
-__device__ __forceinline__ Fq mul(const Fq& a, const Fq& b) {
-  Fq r;
-  mul_k<1>(&r, &a, &b);
   return r;
 }
-__device__ __forceinline__ void mul2(Fq& r0, const Fq& a0, const Fq& b0, Fq& r1, const Fq& a1, const Fq& b1) {
-  Fq a[2] = {a0, a1}, b[2] = {b0, b1}, r[2];
-  mul_k<2>(r, a, b);
-  r0 = r[0];
-  r1 = r[1];
+
+// All limbs zero (the representation of 0 that infinity's ZZ keeps).
+__device__ __forceinline__ bool all_zero(const Fq& a) {
+  int32_t o = 0;
+#pragma unroll
+  for (int i = 0; i < kN; ++i) o |= a.v[i];
+  return o == 0;
 }
-// Three and four independent products, interleaved: more instructions in
-// flight for the reduction's lone waves, where one product's chain of
-// dependent multiply-adds would otherwise wait on its own latency.
-__device__ __forceinline__ void mul3(Fq& r0, const Fq& a0, const Fq& b0, Fq& r1, const Fq& a1, const Fq& b1, Fq& r2,
-                                     const Fq& a2, const Fq& b2) {
-  Fq a[3] = {a0, a1, a2}, b[3] = {b0, b1, b2}, r[3];
-  mul_k<3>(r, a, b);
-  r0 = r[0];
-  r1 = r[1];
-  r2 = r[2];
+
+// a = 0 mod q, for |a| < 8 q.  The multiple k of q that a would be follows
+// from its lowest 28 bits; anything but a k within 8 of 0 (all but one in
+// 2^24 values) is ruled out by it, the rest is compared in full.
+__device__ __forceinline__ bool is_zero(const Fq& a) {
+  const uint32_t k = ((uint32_t)a.v[0] * kInv) & kMask;
+  if (((k + 8u) & kMask) > 16u) return false;
+  const int32_t ks = (int32_t)(k << (32 - kBits)) >> (32 - kBits);
+  int64_t c = 0;
+  int32_t o = 0;
+#pragma unroll
+  for (int i = 0; i < kN; ++i) {
+    c += (int64_t)a.v[i] - (int64_t)ks * kQ28.v[i];
+    o |= i + 1 < kN ? (int32_t)((uint32_t)c & kMask) : (int32_t)c;
+    c >>= kBits;
+  }
+  return o == 0;
 }
-__device__ __forceinline__ void mul4(Fq& r0, const Fq& a0, const Fq& b0, Fq& r1, const Fq& a1, const Fq& b1, Fq& r2,
-                                     const Fq& a2, const Fq& b2, Fq& r3, const Fq& a3, const Fq& b3) {
-  Fq a[4] = {a0, a1, a2, a3}, b[4] = {b0, b1, b2, b3}, r[4];
-  mul_k<4>(r, a, b);
-  r0 = r[0];
-  r1 = r[1];
-  r2 = r[2];
-  r3 = r[3];
+
+// (sum of products - m q) / 2^392, column by column; col(i, acc) adds column
+// i of the products to the accumulator.
+template <class Col>
+__device__ __forceinline__ Fq reduce(Col col) {
+  int32_t m[kN];
+  Fq r;
+  int64_t acc = 0;
+#pragma unroll
+  for (int i = 0; i < kN; ++i) {
+    acc = col(i, acc);
+#pragma unroll
+    for (int j = 0; j < i; ++j) acc += (int64_t)m[j] * -kQ28.v[i - j];
+    m[i] = (int32_t)(((uint32_t)acc * kInv) & kMask);
+    acc += (int64_t)m[i] * -kQ28.v[0];
+    acc >>= kBits;
+  }
+#pragma unroll
+  for (int i = kN; i < 2 * kN - 1; ++i) {
+    acc = col(i, acc);
+#pragma unroll
+    for (int j = i - (kN - 1); j < kN; ++j) acc += (int64_t)m[j] * -kQ28.v[i - j];
+    r.v[i - kN] = (int32_t)((uint32_t)acc & kMask);
+    acc >>= kBits;
+  }
+  r.v[kN - 1] = (int32_t)acc;
+  return r;
 }
-__device__ __forceinline__ Fq sqr(const Fq& a) { return mul(a, a); }
+
+__device__ __forceinline__ int64_t column(const Fq& a, const Fq& b, int i, int64_t acc) {
+#pragma unroll
+  for (int j = 0; j < kN; ++j)
+    if (j <= i && i - j < kN) acc += (int64_t)a.v[j] * b.v[i - j];
+  return acc;
+}
+
+__device__ __forceinline__ Fq mul(const Fq& a, const Fq& b) {
+  return reduce([&](int i, int64_t acc) { return column(a, b, i, acc); });
+}
+
+// a b + c d with one reduction.
+__device__ __forceinline__ Fq mul_add(const Fq& a, const Fq& b, const Fq& c, const Fq& d) {
+  return reduce([&](int i, int64_t acc) { return column(c, d, i, column(a, b, i, acc)); });
+}
+
+__device__ __forceinline__ Fq sqr(const Fq& a) {
+  const Fq t = dbl(a);
+  return reduce([&](int i, int64_t acc) {
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+      if (2 * j < i && i - j < kN) acc += (int64_t)t.v[j] * a.v[i - j];
+      if (2 * j == i) acc += (int64_t)a.v[j] * a.v[j];
+    }
+    return acc;
+  });
+}
 
 // a^-1 = a^(q-2) (Fermat), left-to-right square-and-multiply; a != 0.
 __device__ __forceinline__ Fq inverse(const Fq& a) {
-  // q - 2 differs from q only in the lowest limb (q mod 2^32 >= 2)
+  // q - 2 differs from q only in the lowest word (q mod 2^32 >= 2)
   Fq r = one();
 #pragma unroll 1
-  for (int i = 32 * kN - 1; i >= 0; --i) {
+  for (int i = 32 * kWords - 1; i >= 0; --i) {
     r = sqr(r);
-    const uint32_t e = (i < 32) ? kQ[0] - 2u : kQ[i / 32];
+    const uint32_t e = (i < 32) ? kQ.v[0] - 2u : kQ.v[i / 32];
     if ((e >> (i % 32)) & 1u) r = mul(r, a);
   }
   return r;
+}
+
+// Twelve 32-bit words (a value in [0, 2^384)) to limbs and back.
+__device__ __forceinline__ Fq unpack(const uint32_t (&w)[kWords]) {
+  Fq r;
+#pragma unroll
+  for (int i = 0; i < kN; ++i) {
+    const int k = kBits * i / 32, s = kBits * i % 32;
+    uint32_t x = w[k];
+    if (s) x = k + 1 < kWords ? (uint32_t)((((uint64_t)w[k + 1] << 32) | x) >> s) : x >> s;
+    r.v[i] = (int32_t)(x & kMask);
+  }
+  return r;
+}
+// The canonical value in [0, q) of a product's result.
+__device__ __forceinline__ void pack_canonical(uint32_t (&w)[kWords], const Fq& a) {
+  Fq x;  // a + 2 q, in (0.8 q, 2.2 q)
+#pragma unroll
+  for (int i = 0; i < kN; ++i) x.v[i] = a.v[i] + 2 * kQ28.v[i];
+  x = normalise(x);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    Fq d;
+#pragma unroll
+    for (int i = 0; i < kN; ++i) d.v[i] = x.v[i] - kQ28.v[i];
+    d = normalise(d);
+    const bool ge = d.v[kN - 1] >= 0;
+#pragma unroll
+    for (int i = 0; i < kN; ++i) x.v[i] = ge ? d.v[i] : x.v[i];
+  }
+#pragma unroll
+  for (int k = 0; k < kWords; ++k) {
+    const int i = 32 * k / kBits, s = 32 * k % kBits;
+    uint64_t t = (uint64_t)(uint32_t)x.v[i] >> s;
+    t |= (uint64_t)(uint32_t)x.v[i + 1] << (kBits - s);
+    if (i + 2 < kN) t |= (uint64_t)(uint32_t)x.v[i + 2] << (2 * kBits - s);
+    w[k] = (uint32_t)t;
+  }
 }
 
 }  // namespace fq

@@ -19,17 +19,20 @@
 // * Bucket accumulation: the sorted entries are cut into equal runs, one per
 //   lane, across bucket boundaries; a lane adds its run's points into XYZZ
 //   accumulators with mixed (XYZZ + affine) additions, 8 multiplications
-//   and 2 squarings each in four rounds of independent products, and the
-//   segments at the runs' ends then combine per bucket.  XYZZ coordinates
-//   (x = X / ZZ, y = Y / ZZZ) keep additions free of inversions.
+//   and 2 squarings each, and the segments at the runs' ends then combine
+//   per bucket.  XYZZ coordinates (x = X / ZZ, y = Y / ZZZ) keep additions
+//   free of inversions.
 // * Bucket reduction by bits: sum_k k B_k = sum_b 2^b G_b with
-//   G_b = sum of the buckets whose index has bit b set.  The G_b are
-//   independent reductions (chunk sums formed once, chunks per lane, then
-//   trees in LDS), and the c terms 2^b G_b are doubled in parallel and
-//   summed by a tree: a critical path of a few dozen point operations,
-//   where the running-sum method is a serial chain of 2^(c+1) additions.
+//   G_b = sum of the buckets whose index has bit b set, formed by a tree over
+//   the buckets that sums the odd nodes of every level beside the nodes
+//   themselves; the c terms 2^b G_b are doubled in parallel and summed by a
+//   tree: a critical path of a few dozen point operations, where the
+//   running-sum method is a serial chain of 2^(c+1) additions.
+// * Everything after the accumulation is bound by the latency of point
+//   operations in few waves: there four lanes share a point, one coordinate
+//   each, and an addition is four products in sequence instead of fourteen.
 //
-// Field arithmetic: fq.hpp (12 x 32-bit limbs, Montgomery FIPS products).
+// Field arithmetic: fq.hpp (14 x 28-bit limbs).
 // Scalars arrive as the NTT library's Montgomery limbs over BLS12-381 Fr and
 // are converted with one product by 1.
 #include <hip/hip_runtime.h>
@@ -54,6 +57,9 @@ struct Xyzz {
   Fq X, Y, ZZ, ZZZ;
 };
 
+// Coordinates are products' results or normalised, so limbs 0 .. 12 are in
+// [0, 2^28) and values within (-2 q, 4 q).  Infinity has ZZ = ZZZ = 0 with all
+// limbs zero; no other point has.
 __device__ __forceinline__ Xyzz infinity() {
   Xyzz r;
   r.X = fq::one();
@@ -62,8 +68,6 @@ __device__ __forceinline__ Xyzz infinity() {
   r.ZZZ = fq::zero();
   return r;
 }
-
-__device__ __forceinline__ bool is_inf(const Xyzz& p) { return fq::is_zero(p.ZZ); }
 
 __device__ __forceinline__ Xyzz from_affine(const Affine& a) {
   Xyzz r;
@@ -76,138 +80,216 @@ __device__ __forceinline__ Xyzz from_affine(const Affine& a) {
 
 // 2 P in XYZZ (y^2 = x^3 + b, a = 0): U = 2Y, V = U^2, W = U V, S = X V,
 // M = 3 X^2; X3 = M^2 - 2S, Y3 = M (S - X3) - W Y, ZZ3 = V ZZ, ZZZ3 = W ZZZ.
-// Infinity (ZZ = 0) and points with Y = 0 give ZZ3 = 0.
-// The products run in three rounds of independent ones (2, 4, 3).
 __device__ __forceinline__ Xyzz dbl(const Xyzz& p) {
   const Fq U = fq::dbl(p.Y);
-  Fq V, XX;
-  fq::mul2(V, U, U, XX, p.X, p.X);
-  const Fq M = fq::add(fq::dbl(XX), XX);
-  Fq W, S, MM;
+  const Fq V = fq::sqr(U), XX = fq::sqr(p.X);
+  const Fq W = fq::mul(U, V), S = fq::mul(p.X, V);
+  const Fq M = fq::normalise(fq::add(fq::dbl(XX), XX));
   Xyzz r;
-  fq::mul4(W, U, V, S, p.X, V, MM, M, M, r.ZZ, V, p.ZZ);
-  r.X = fq::sub(MM, fq::dbl(S));
-  Fq t, WY;
-  fq::mul3(t, M, fq::sub(S, r.X), WY, W, p.Y, r.ZZZ, W, p.ZZZ);
-  r.Y = fq::sub(t, WY);
+  r.X = fq::normalise(fq::sub(fq::sqr(M), fq::dbl(S)));
+  r.Y = fq::mul_add(M, fq::sub(S, r.X), fq::neg(W), p.Y);
+  r.ZZ = fq::mul(V, p.ZZ);
+  r.ZZZ = fq::mul(W, p.ZZZ);
   return r;
 }
 
-// 2 A for an affine point: U = 2y, V = U^2, W = U V, S = x V, M = 3 x^2;
-// X3 = M^2 - 2S, Y3 = M (S - X3) - W y, ZZ3 = V, ZZZ3 = W.
+// 2 A for an affine point (ZZ = ZZZ = 1).
 __device__ __forceinline__ Xyzz dbl_affine(const Affine& a) {
   const Fq U = fq::dbl(a.y);
-  Fq V, XX;
-  fq::mul2(V, U, U, XX, a.x, a.x);
-  Fq W, S;
-  fq::mul2(W, U, V, S, a.x, V);
-  const Fq M = fq::add(fq::dbl(XX), XX);
+  const Fq V = fq::sqr(U), XX = fq::sqr(a.x);
+  const Fq W = fq::mul(U, V), S = fq::mul(a.x, V);
+  const Fq M = fq::normalise(fq::add(fq::dbl(XX), XX));
   Xyzz r;
-  r.X = fq::sub(fq::sqr(M), fq::dbl(S));
-  Fq t, WY;
-  fq::mul2(t, M, fq::sub(S, r.X), WY, W, a.y);
-  r.Y = fq::sub(t, WY);
+  r.X = fq::normalise(fq::sub(fq::sqr(M), fq::dbl(S)));
+  r.Y = fq::mul_add(M, fq::sub(S, r.X), fq::neg(W), a.y);
   r.ZZ = V;
   r.ZZZ = W;
   return r;
 }
 
-// P + A with A affine: U2 = x2 ZZ1, S2 = y2 ZZZ1, P = U2 - X1, R = S2 - Y1,
-// PP = P^2, PPP = P PP, Q = X1 PP; X3 = R^2 - PPP - 2Q,
-// Y3 = R (Q - X3) - Y1 PPP, ZZ3 = ZZ1 PP, ZZZ3 = ZZZ1 PPP.  P = 0 means
-// x-coordinates agree: the points are equal (double A) or opposite
-// (infinity).
-__device__ __forceinline__ Xyzz add_mixed(const Xyzz& p, const Affine& a) {
-  if (is_inf(p)) return from_affine(a);
-  Fq U2, S2;
-  fq::mul2(U2, a.x, p.ZZ, S2, a.y, p.ZZZ);
-  const Fq P = fq::sub(U2, p.X);
-  const Fq R = fq::sub(S2, p.Y);
-  if (fq::is_zero(P)) return fq::is_zero(R) ? dbl_affine(a) : infinity();
-  Fq PP, RR;
-  fq::mul2(PP, P, P, RR, R, R);
-  Fq PPP, Qx;
-  fq::mul2(PPP, P, PP, Qx, p.X, PP);
+// P + A with A affine, P not infinity: U2 = x2 ZZ1, S2 = y2 ZZZ1,
+// P = U2 - X1, R = S2 - Y1, PP = P^2, PPP = P PP, Q = X1 PP;
+// X3 = R^2 - PPP - 2Q, Y3 = R (Q - X3) - Y1 PPP, ZZ3 = ZZ1 PP,
+// ZZZ3 = ZZZ1 PPP.  P = 0 means x-coordinates agree: the points are equal
+// (double A) or opposite (`cancelled`: infinity).
+__device__ __forceinline__ Xyzz add_mixed(const Xyzz& p, const Affine& a, bool& cancelled) {
+  const Fq P = fq::sub(fq::mul(a.x, p.ZZ), p.X);
+  const Fq R = fq::sub(fq::mul(a.y, p.ZZZ), p.Y);
+  if (fq::is_zero(P)) {
+    cancelled = !fq::is_zero(R);
+    return cancelled ? infinity() : dbl_affine(a);
+  }
+  const Fq PP = fq::sqr(P);
+  const Fq PPP = fq::mul(P, PP), Q = fq::mul(p.X, PP);
   Xyzz r;
-  r.X = fq::sub(fq::sub(RR, PPP), fq::dbl(Qx));
-  Fq t, YP;
-  fq::mul4(t, R, fq::sub(Qx, r.X), YP, p.Y, PPP, r.ZZ, p.ZZ, PP, r.ZZZ, p.ZZZ, PPP);
-  r.Y = fq::sub(t, YP);
+  r.X = fq::normalise(fq::sub(fq::sub(fq::sqr(R), PPP), fq::dbl(Q)));
+  r.Y = fq::mul_add(R, fq::sub(Q, r.X), fq::neg(p.Y), PPP);
+  r.ZZ = fq::mul(p.ZZ, PP);
+  r.ZZZ = fq::mul(p.ZZZ, PPP);
   return r;
 }
 
-// P1 + P2, both XYZZ: U1 = X1 ZZ2, U2 = X2 ZZ1, S1 = Y1 ZZZ2, S2 = Y2 ZZZ1,
-// P = U2 - U1, R = S2 - S1, PP = P^2, PPP = P PP, Q = U1 PP;
-// X3 = R^2 - PPP - 2Q, Y3 = R (Q - X3) - S1 PPP, ZZ3 = ZZ1 ZZ2 PP,
-// ZZZ3 = ZZZ1 ZZZ2 PPP.
-// The 14 products run in four rounds of independent ones (4, 2, 4, 4).
-__device__ __forceinline__ Xyzz add(const Xyzz& p, const Xyzz& q) {
-  if (is_inf(p)) return q;
-  if (is_inf(q)) return p;
-  Fq U1, U2, S1, S2;
-  fq::mul4(U1, p.X, q.ZZ, U2, q.X, p.ZZ, S1, p.Y, q.ZZZ, S2, q.Y, p.ZZZ);
-  const Fq P = fq::sub(U2, U1);
-  const Fq R = fq::sub(S2, S1);
-  if (fq::is_zero(P)) return fq::is_zero(R) ? dbl(p) : infinity();
-  Fq PP, RR;
-  fq::mul2(PP, P, P, RR, R, R);
-  Fq PPP, Qx, z2, z3;
-  fq::mul4(PPP, P, PP, Qx, U1, PP, z2, p.ZZ, q.ZZ, z3, p.ZZZ, q.ZZZ);
-  Xyzz r;
-  r.X = fq::sub(fq::sub(RR, PPP), fq::dbl(Qx));
-  Fq t, SP;
-  fq::mul4(t, R, fq::sub(Qx, r.X), SP, S1, PPP, r.ZZ, z2, PP, r.ZZZ, z3, PPP);
-  r.Y = fq::sub(t, SP);
+// A packed affine point: x then y, twelve 32-bit words each, as three 16-byte
+// loads.
+struct Packed {
+  uint4 v[6];
+};
+__device__ __forceinline__ Packed load_packed(const uint32_t* __restrict__ pts, uint64_t i) {
+  const uint4* q = reinterpret_cast<const uint4*>(pts + kPointWords * i);
+  Packed r;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) r.v[k] = q[k];
   return r;
 }
-
-__device__ __forceinline__ Affine load_affine(const uint32_t* __restrict__ pts, uint64_t i) {
-  const uint4* q = reinterpret_cast<const uint4*>(pts + 24 * i);
-  Affine a;
+__device__ __forceinline__ Affine unpack(const Packed& p) {
+  uint32_t x[fq::kWords], y[fq::kWords];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const uint4 u = q[k], w = q[3 + k];
-    a.x.v[4 * k] = u.x, a.x.v[4 * k + 1] = u.y, a.x.v[4 * k + 2] = u.z, a.x.v[4 * k + 3] = u.w;
-    a.y.v[4 * k] = w.x, a.y.v[4 * k + 1] = w.y, a.y.v[4 * k + 2] = w.z, a.y.v[4 * k + 3] = w.w;
+    const uint4 u = p.v[k], w = p.v[3 + k];
+    x[4 * k] = u.x, x[4 * k + 1] = u.y, x[4 * k + 2] = u.z, x[4 * k + 3] = u.w;
+    y[4 * k] = w.x, y[4 * k + 1] = w.y, y[4 * k + 2] = w.z, y[4 * k + 3] = w.w;
   }
-  return a;
+  return Affine{fq::unpack(x), fq::unpack(y)};
 }
-
-__device__ __forceinline__ void store_affine(uint32_t* __restrict__ pts, uint64_t i, const Affine& a) {
+__device__ __forceinline__ void store_affine(uint32_t* __restrict__ pts, uint64_t i, const Fq& x, const Fq& y) {
+  uint32_t wx[fq::kWords], wy[fq::kWords];
+  fq::pack_canonical(wx, x);
+  fq::pack_canonical(wy, y);
 #pragma unroll
-  for (int k = 0; k < fq::kN; ++k) {
-    pts[24 * i + k] = a.x.v[k];
-    pts[24 * i + 12 + k] = a.y.v[k];
+  for (int k = 0; k < fq::kWords; ++k) {
+    pts[kPointWords * i + k] = wx[k];
+    pts[kPointWords * i + fq::kWords + k] = wy[k];
   }
 }
 
+// Working points in memory: four coordinates of fourteen limbs.
+__device__ __forceinline__ void store_xyzz(uint32_t* __restrict__ p, uint64_t i, const Xyzz& a) {
+  int2* q = reinterpret_cast<int2*>(p + kAccWords * i);
+#pragma unroll
+  for (int k = 0; k < fq::kN / 2; ++k) {
+    q[k] = make_int2(a.X.v[2 * k], a.X.v[2 * k + 1]);
+    q[7 + k] = make_int2(a.Y.v[2 * k], a.Y.v[2 * k + 1]);
+    q[14 + k] = make_int2(a.ZZ.v[2 * k], a.ZZ.v[2 * k + 1]);
+    q[21 + k] = make_int2(a.ZZZ.v[2 * k], a.ZZZ.v[2 * k + 1]);
+  }
+}
 __device__ __forceinline__ Xyzz load_xyzz(const uint32_t* __restrict__ p, uint64_t i) {
+  const int2* q = reinterpret_cast<const int2*>(p + kAccWords * i);
   Xyzz r;
 #pragma unroll
-  for (int k = 0; k < fq::kN; ++k) {
-    r.X.v[k] = p[48 * i + k];
-    r.Y.v[k] = p[48 * i + 12 + k];
-    r.ZZ.v[k] = p[48 * i + 24 + k];
-    r.ZZZ.v[k] = p[48 * i + 36 + k];
+  for (int k = 0; k < fq::kN / 2; ++k) {
+    const int2 x = q[k], y = q[7 + k], z = q[14 + k], t = q[21 + k];
+    r.X.v[2 * k] = x.x, r.X.v[2 * k + 1] = x.y;
+    r.Y.v[2 * k] = y.x, r.Y.v[2 * k + 1] = y.y;
+    r.ZZ.v[2 * k] = z.x, r.ZZ.v[2 * k + 1] = z.y;
+    r.ZZZ.v[2 * k] = t.x, r.ZZZ.v[2 * k + 1] = t.y;
   }
   return r;
-}
-
-__device__ __forceinline__ void store_xyzz(uint32_t* __restrict__ p, uint64_t i, const Xyzz& a) {
-#pragma unroll
-  for (int k = 0; k < fq::kN; ++k) {
-    p[48 * i + k] = a.X.v[k];
-    p[48 * i + 12 + k] = a.Y.v[k];
-    p[48 * i + 24 + k] = a.ZZ.v[k];
-    p[48 * i + 36 + k] = a.ZZZ.v[k];
-  }
 }
 
 // ---------------------------------------------------------------------------
-// Precomputation: table[w n + i] = 2^(c w) P_i, affine.  One lane per point
-// walks the windows with c doublings each, keeping the XYZZ multiples in
-// `scratch`, then turns all W of them affine with one inversion (prefix
-// products of the ZZZ, Fermat inversion, back-substitution; 1/ZZ = (ZZ/ZZZ)^2).
+// Points shared by four lanes: lane 0 of a quad holds X, lane 1 Y, lane 2 ZZ
+// and lane 3 ZZZ.  All four lanes are active in every operation, so that
+// limbs can move between them by DPP.  A lone wave issues one multiply-add in
+// eight cycles, whatever its parallelism, so an addition's fourteen products
+// cost it fourteen times one product's latency in one lane and four times in
+// four (addition 16 -> 6 us, doubling 15 -> 5 us, one wave per SIMD).
+
+template <int A, int B, int C, int D>
+__device__ __forceinline__ int quad_perm(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, A | (B << 2) | (C << 4) | (D << 6), 0xf, 0xf, true);
+}
+template <int A, int B, int C, int D>
+__device__ __forceinline__ Fq quad_perm(const Fq& a) {
+  Fq r;
+#pragma unroll
+  for (int i = 0; i < fq::kN; ++i) r.v[i] = quad_perm<A, B, C, D>(a.v[i]);
+  return r;
+}
+template <int L>
+__device__ __forceinline__ Fq bcast(const Fq& a) {
+  return quad_perm<L, L, L, L>(a);
+}
+__device__ __forceinline__ Fq sel(bool c, const Fq& a, const Fq& b) {
+  Fq r;
+#pragma unroll
+  for (int i = 0; i < fq::kN; ++i) r.v[i] = c ? a.v[i] : b.v[i];
+  return r;
+}
+__device__ __forceinline__ uint32_t quad_lane() { return threadIdx.x & 3u; }
+
+// Infinity's coordinate of this lane.
+__device__ __forceinline__ Fq q_infinity() { return sel(quad_lane() < 2, fq::one(), fq::zero()); }
+
+__device__ __forceinline__ Fq q_dbl(const Fq& a) {
+  const uint32_t q = quad_lane();
+  const Fq u = fq::dbl(a);  // lane 1: U
+  const Fq r1 = fq::sqr(sel(q == 1, u, a));  // lane 0: X^2, lane 1: V
+  const Fq V = bcast<1>(r1);
+  const Fq M = fq::normalise(fq::add(fq::dbl(r1), r1));  // lane 0
+  // lane 0: M^2, lane 1: W = U V, lane 2: ZZ V, lane 3: S = X V
+  const Fq x2 = sel(q == 0, M, sel(q == 1, u, sel(q == 2, a, bcast<0>(a))));
+  const Fq r2 = fq::mul(x2, sel(q == 0, M, V));
+  const Fq S = bcast<3>(r2), W = bcast<1>(r2);
+  const Fq X3 = fq::normalise(fq::sub(r2, fq::dbl(S)));  // lane 0
+  // lane 0: M (S - X3), lane 1: W Y, lane 3: W ZZZ
+  const Fq r3 = fq::mul(sel(q == 0, M, a), sel(q == 0, fq::sub(S, X3), W));
+  const Fq Y3 = fq::normalise(fq::sub(bcast<0>(r3), r3));
+  return sel(q == 0, X3, sel(q == 1, Y3, sel(q == 2, r2, r3)));
+}
+
+// P1 + P2: U1 = X1 ZZ2, U2 = X2 ZZ1, S1 = Y1 ZZZ2, S2 = Y2 ZZZ1,
+// P = U2 - U1, R = S2 - S1, PP = P^2, PPP = P PP, Q = U1 PP;
+// X3 = R^2 - PPP - 2Q, Y3 = R (Q - X3) - S1 PPP, ZZ3 = ZZ1 ZZ2 PP,
+// ZZZ3 = ZZZ1 ZZZ2 PPP.
+__device__ __forceinline__ Fq q_add(const Fq& a, const Fq& b) {
+  const uint32_t q = quad_lane();
+  const Fq r1 = fq::mul(a, quad_perm<2, 3, 0, 1>(b));  // U1, S1, U2, S2
+  const Fq o = quad_perm<2, 3, 0, 1>(r1);
+  const Fq d = sel(q < 2, fq::sub(o, r1), fq::sub(r1, o));  // P, R, P, R
+  const Fq r2 = fq::mul(sel(q < 2, d, a), sel(q < 2, d, b));  // PP, R^2, ZZ1 ZZ2, ZZZ1 ZZZ2
+  // PPP, Q, ZZ3, PPP
+  const Fq x3 = sel(q == 1, bcast<0>(r1), sel(q == 2, r2, bcast<2>(d)));
+  const Fq r3 = fq::mul(x3, bcast<0>(r2));
+  const Fq X3 = fq::normalise(fq::sub(fq::sub(r2, bcast<0>(r3)), fq::dbl(r3)));  // lane 1
+  // S1 PPP, R (Q - X3), -, ZZZ3
+  const Fq x4 = sel(q == 0, bcast<1>(r1), sel(q == 1, d, r2));
+  const Fq r4 = fq::mul(x4, sel(q == 1, fq::sub(r3, X3), r3));
+  const Fq Y3 = fq::normalise(fq::sub(r4, bcast<0>(r4)));  // lane 1
+  Fq r = sel(q == 0, bcast<1>(X3), sel(q == 1, Y3, sel(q == 2, r3, r4)));
+  const bool ainf = quad_perm<2, 2, 2, 2>((int)fq::all_zero(a)) != 0;
+  const bool binf = quad_perm<2, 2, 2, 2>((int)fq::all_zero(b)) != 0;
+  const int dz = (int)fq::is_zero(d);
+  const bool same_x = quad_perm<0, 0, 0, 0>(dz) != 0, same_y = quad_perm<1, 1, 1, 1>(dz) != 0;
+  if (__any(same_x && !ainf && !binf)) {  // equal or opposite points
+    const Fq two = q_dbl(a);
+    r = same_x ? sel(same_y, two, q_infinity()) : r;
+  }
+  return sel(ainf, b, sel(binf, a, r));
+}
+
+__device__ __forceinline__ Fq q_load(const uint32_t* p, uint64_t i) {
+  const int2* s = reinterpret_cast<const int2*>(p + kAccWords * i + fq::kN * quad_lane());
+  Fq r;
+#pragma unroll
+  for (int k = 0; k < fq::kN / 2; ++k) {
+    const int2 x = s[k];
+    r.v[2 * k] = x.x, r.v[2 * k + 1] = x.y;
+  }
+  return r;
+}
+__device__ __forceinline__ void q_store(uint32_t* p, uint64_t i, const Fq& a) {
+  int2* s = reinterpret_cast<int2*>(p + kAccWords * i + fq::kN * quad_lane());
+#pragma unroll
+  for (int k = 0; k < fq::kN / 2; ++k) s[k] = make_int2(a.v[2 * k], a.v[2 * k + 1]);
+}
+
+// ---------------------------------------------------------------------------
+// Precomputation: table[w n + i] = 2^(c w) P_i, affine, Montgomery form 2^392.
+// One lane per point walks the windows with c doublings each, keeping the
+// XYZZ multiples in `scratch`, then turns all W of them affine with one
+// inversion (prefix products of the ZZZ, Fermat inversion, back-substitution;
+// 1/ZZ = (ZZ/ZZZ)^2).
 
 // Points first .. first + count of n; scratch holds `count` points' rows.
 __global__ void __launch_bounds__(128) precompute_kernel(const uint32_t* __restrict__ pts, uint64_t n,
@@ -217,38 +299,38 @@ __global__ void __launch_bounds__(128) precompute_kernel(const uint32_t* __restr
   const uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= count) return;
   const uint64_t i = first + k;
-  const Affine a = load_affine(pts, i);
-  store_affine(table, i, a);
+  Affine a = unpack(load_packed(pts, i));
+  a.x = fq::mul(a.x, fq::constant(fq::kTo392));
+  a.y = fq::mul(a.y, fq::constant(fq::kTo392));
+  store_affine(table, i, a.x, a.y);
   if (windows == 1) return;
-  // scratch rows of this point: windows x (XYZZ, prefix product of ZZZ)
-  uint32_t* my = scratch + k * windows * 60;
+  // scratch rows of this point: windows x XYZZ, then the prefix products of ZZZ
+  uint32_t* my = scratch + k * windows * kScratchWords;
+  uint32_t* prefix = my + kAccWords * windows;
   Xyzz p = from_affine(a);
   Fq pre = fq::one();
+#pragma unroll 1
   for (int w = 1; w < windows; ++w) {
+#pragma unroll 1
     for (int d = 0; d < c; ++d) p = dbl(p);
-    store_xyzz(my, w, p);  // 48-word slots at 48 w ...
+    store_xyzz(my, w, p);
     pre = fq::mul(pre, p.ZZZ);
 #pragma unroll
-    for (int k = 0; k < fq::kN; ++k) my[48 * windows + 12 * w + k] = pre.v[k];
+    for (int l = 0; l < fq::kN; ++l) prefix[fq::kN * w + l] = (uint32_t)pre.v[l];
   }
   Fq inv = fq::inverse(pre);  // 1 / prod_w ZZZ_w
+#pragma unroll 1
   for (int w = windows - 1; w >= 1; --w) {
     const Xyzz q = load_xyzz(my, w);
-    Fq prev;
+    Fq prev = fq::one();
     if (w > 1) {
 #pragma unroll
-      for (int k = 0; k < fq::kN; ++k) prev.v[k] = my[48 * windows + 12 * (w - 1) + k];
-    } else {
-      prev = fq::one();
+      for (int l = 0; l < fq::kN; ++l) prev.v[l] = (int32_t)prefix[fq::kN * (w - 1) + l];
     }
-    Fq t, nxt;
-    fq::mul2(t, inv, prev, nxt, inv, q.ZZZ);  // t = 1 / ZZZ_w; inv <- 1 / prod_{v<w} ZZZ_v
-    inv = nxt;
-    const Fq iz = fq::mul(q.ZZ, t);  // 1 / Z
-    const Fq izz = fq::sqr(iz);      // 1 / ZZ
-    Affine r;
-    fq::mul2(r.x, q.X, izz, r.y, q.Y, t);
-    store_affine(table, (uint64_t)w * n + i, r);
+    const Fq t = fq::mul(inv, prev);   // 1 / ZZZ_w
+    inv = fq::mul(inv, q.ZZZ);         // 1 / prod_{v<w} ZZZ_v
+    const Fq izz = fq::sqr(fq::mul(q.ZZ, t));  // (1 / Z)^2
+    store_affine(table, (uint64_t)w * n + i, fq::mul(q.X, izz), fq::mul(q.Y, t));
   }
 }
 
@@ -395,7 +477,7 @@ __global__ void __launch_bounds__(kScanThreads) scan_kernel(const uint32_t* __re
     }
   }
   if (t == kScanThreads - 1) offsets[nb] = part[kScanThreads - 1];
-  if (t == 0) *big_count = 0u;  // the combine step's list of large buckets starts empty
+  if (t < 2) big_count[t] = 0u;  // the combine step's lists of large buckets start empty
 }
 
 // entries[offsets[d] + (earlier groups' count of d) + rank] = w n + i for
@@ -433,7 +515,7 @@ __device__ __forceinline__ uint32_t lane_span(uint32_t E, uint32_t lanes, uint32
 
 constexpr uint32_t kAccumulateThreads = 128;
 
-__global__ void __launch_bounds__(kAccumulateThreads) accumulate_kernel(const uint32_t* __restrict__ table,
+__global__ void __launch_bounds__(kAccumulateThreads, 2) accumulate_kernel(const uint32_t* __restrict__ table,
                                                          const uint32_t* __restrict__ entries,
                                                          const uint32_t* __restrict__ offsets, uint32_t nb,
                                                          uint32_t lanes, uint32_t kmin, uint32_t* __restrict__ head,
@@ -454,193 +536,228 @@ __global__ void __launch_bounds__(kAccumulateThreads) accumulate_kernel(const ui
     if (offsets[mid] <= lo_pos) lo = mid; else hi = mid;
   }
   uint32_t cur = lo, next = offsets[cur + 1];
-  bool first = true;
+  bool first = true, empty = true;  // empty: the accumulator is infinity
   Xyzz acc = infinity();
+  Packed next_pt = load_packed(table, entries[lo_pos]);
+#pragma unroll 1
   for (uint32_t k = lo_pos; k < end; ++k) {
+    const Packed pt = next_pt;  // loaded one addition ahead
+    if (k + 1 < end) next_pt = load_packed(table, entries[k + 1]);
     if (k == next) {  // bucket cur ends before position k
       if (first) store_xyzz(head, j, acc); else store_xyzz(buckets, cur, acc);
       first = false;
-      acc = infinity();
+      empty = true;
       do {
         ++cur;
         next = offsets[cur + 1];
       } while (next <= k);  // skip empty buckets
     }
-    acc = add_mixed(acc, load_affine(table, entries[k]));
+    const Affine a = unpack(pt);
+    if (empty) {
+      acc = from_affine(a);
+      empty = false;
+    } else {
+      acc = add_mixed(acc, a, empty);
+    }
   }
   if (first) store_xyzz(head, j, acc); else store_xyzz(tail, j, acc);
 }
 
 // Bucket d from the lanes' segments: the segment in the lane holding its
 // first position (that lane's head or tail), plus the heads of the lanes
-// that start inside it.  A bucket that begins and ends strictly inside one
-// lane's run was stored by that lane; an empty bucket is infinity.  A bucket
-// spanning more than kCombineSerial runs (skewed scalars: many equal
-// digits) is listed in big[] for big_combine_kernel instead of being summed
-// by one lane.
+// that start inside it, by one quad.  A bucket that begins and ends strictly
+// inside one lane's run was stored by that lane; an empty bucket is infinity.
+// A bucket spanning more than kCombineSerial runs (skewed scalars: many equal
+// digits) is listed for the big-bucket kernels, kBigRuns runs an item.
 
-__global__ void __launch_bounds__(128) combine_kernel(const uint32_t* __restrict__ offsets, uint32_t nb,
+__global__ void __launch_bounds__(256) combine_kernel(const uint32_t* __restrict__ offsets, uint32_t nb,
                                                       uint32_t lanes, uint32_t kmin,
                                                       const uint32_t* __restrict__ head,
                                                       const uint32_t* __restrict__ tail,
-                                                      uint32_t* __restrict__ buckets, uint32_t* __restrict__ big,
-                                                      uint32_t* __restrict__ big_count) {
-  const uint32_t d = blockIdx.x * blockDim.x + threadIdx.x;
-  if (d >= nb) return;
-  const uint32_t lo = offsets[d], hi = offsets[d + 1];
-  if (lo == hi) {
-    store_xyzz(buckets, d, infinity());
-    return;
-  }
+                                                      uint32_t* __restrict__ buckets, BigLists big) {
+  const uint32_t d = (blockIdx.x * blockDim.x + threadIdx.x) / 4;
+  const uint32_t lo = d < nb ? offsets[d] : 0u, hi = d < nb ? offsets[d + 1] : 0u;
   const uint32_t E = offsets[nb];
   const uint32_t K = lane_span(E, lanes, kmin);
-  const uint32_t jl = lo / K, jh = (hi - 1) / K;
-  if (jh - jl > kCombineSerial) {
-    big[atomicAdd(big_count, 1u)] = d;
-    return;
+  uint32_t j = 1, jh = 0;  // runs j .. jh are still to be added
+  bool store = d < nb;
+  Fq acc = q_infinity();
+  if (lo < hi) {
+    const uint32_t jl = lo / K;
+    jh = (hi - 1) / K;
+    j = jl + 1;
+    const uint64_t run_end = min<uint64_t>((uint64_t)(jl + 1) * K, E);
+    if (jh - jl > kCombineSerial) {
+      if (quad_lane() == 0) {
+        const uint32_t items = (jh - jl + kBigRuns - 1) / kBigRuns;
+        const uint32_t at = atomicAdd(&big.count[1], items);
+        const uint32_t b = atomicAdd(&big.count[0], 1u);
+        big.bucket[b] = make_uint4(d, at, items, 0u);
+        for (uint32_t k = 0; k < items; ++k) big.item[at + k] = b;
+      }
+      store = false;
+      jh = 0;
+    } else if (lo == jl * K) {
+      acc = q_load(head, jl);
+    } else if (hi >= run_end) {
+      acc = q_load(tail, jl);
+    } else {
+      store = false;  // stored by its lane
+    }
   }
-  const uint64_t run_end = min<uint64_t>((uint64_t)(jl + 1) * K, E);
-  Xyzz acc;
-  if (lo == jl * K) acc = load_xyzz(head, jl);
-  else if (hi >= run_end) acc = load_xyzz(tail, jl);
-  else return;
-  for (uint32_t j = jl + 1; j <= jh; ++j) acc = add(acc, load_xyzz(head, j));
-  store_xyzz(buckets, d, acc);
+  while (__any(j <= jh)) {
+    const Fq x = j <= jh ? q_load(head, j) : q_infinity();
+    acc = q_add(acc, x);
+    ++j;
+  }
+  if (store) q_store(buckets, d, acc);
 }
 
-// Tree sum in LDS of the workgroup's points p[t] (t < blockDim.x, a power of
-// two): log2(blockDim.x) rounds of pairwise additions.  Returns the total in
-// every thread.
-__device__ __forceinline__ Xyzz lds_tree_sum(const Xyzz& p, Xyzz* sh) {
-  const uint32_t t = threadIdx.x;
-  sh[t] = p;
+// Sum of the workgroup's points, one per quad, in quad 0 (a power of two of
+// quads; sh: one point per quad).
+__device__ __forceinline__ Fq quads_sum(Fq p, uint32_t* sh) {
+  const uint32_t g = threadIdx.x / 4;
+  q_store(sh, g, p);
   __syncthreads();
-  for (uint32_t half = blockDim.x >> 1; half > 0; half >>= 1) {
-    if (t < half) sh[t] = add(sh[t], sh[t + half]);
+  for (uint32_t half = blockDim.x / 8; half > 0; half >>= 1) {
+    const bool mine = g < half;
+    if (__any(mine)) {
+      p = q_add(p, mine ? q_load(sh, g + half) : q_infinity());
+    }
+    __syncthreads();
+    if (mine) q_store(sh, g, p);
     __syncthreads();
   }
-  return sh[0];
+  return p;
 }
 
-// A listed bucket (workgroup b takes big[b] while b < *big_count): its
-// first segment (it spans more than one run, so that is the head or the
-// tail of its first lane) and the heads of the runs inside it, summed by
-// kBigThreads lanes with strided shares and a tree.  At most
-// lanes / kCombineSerial + 1 buckets can be listed.
 constexpr int kBigThreads = 256;
 
-__global__ void __launch_bounds__(kBigThreads) big_combine_kernel(const uint32_t* __restrict__ offsets, uint32_t nb,
-                                                                  uint32_t lanes, uint32_t kmin,
-                                                                  const uint32_t* __restrict__ head,
-                                                                  const uint32_t* __restrict__ tail,
-                                                                  const uint32_t* __restrict__ big,
-                                                                  const uint32_t* __restrict__ big_count,
-                                                                  uint32_t* __restrict__ buckets) {
-  __shared__ Xyzz sh[kBigThreads];
-  if (blockIdx.x >= *big_count) return;  // the same for every thread of the workgroup
-  const uint32_t d = big[blockIdx.x];
-  const uint32_t lo = offsets[d], hi = offsets[d + 1];
+// One item of a listed bucket: the heads of kBigRuns of the runs that start
+// inside it, and with the first item the segment of the run it starts in (it
+// spans more than one run, so that is the head or the tail of that lane).
+__global__ void __launch_bounds__(kBigThreads) big_item_kernel(const uint32_t* __restrict__ offsets, uint32_t nb,
+                                                               uint32_t lanes, uint32_t kmin,
+                                                               const uint32_t* __restrict__ head,
+                                                               const uint32_t* __restrict__ tail, BigLists big) {
+  __shared__ uint32_t sh[kBigThreads / 4 * kAccWords];
+  const uint32_t items = big.count[1], g = threadIdx.x / 4;
   const uint32_t E = offsets[nb];
   const uint32_t K = lane_span(E, lanes, kmin);
-  const uint32_t jl = lo / K, jh = (hi - 1) / K;
-  Xyzz acc = infinity();
-  if (threadIdx.x == 0) acc = lo == jl * K ? load_xyzz(head, jl) : load_xyzz(tail, jl);
-  for (uint32_t j = jl + 1 + threadIdx.x; j <= jh; j += kBigThreads) acc = add(acc, load_xyzz(head, j));
-  const Xyzz total = lds_tree_sum(acc, sh);
-  if (threadIdx.x == 0) store_xyzz(buckets, d, total);
+  for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {  // the same for every thread of the workgroup
+    const uint4 b = big.bucket[big.item[it]];
+    const uint32_t d = b.x, part = it - b.y;
+    const uint32_t lo = offsets[d], hi = offsets[d + 1];
+    const uint32_t jl = lo / K, jh = (hi - 1) / K;
+    Fq acc = q_infinity();
+    if (part == 0 && g == 0) acc = lo == jl * K ? q_load(head, jl) : q_load(tail, jl);
+    const uint32_t first = jl + 1 + part * kBigRuns;
+    for (uint32_t k = 0; k < kBigRuns; k += kBigThreads / 4) {
+      const uint32_t j = first + k + g;
+      const bool have = j <= jh;
+      if (__any(have)) acc = q_add(acc, have ? q_load(head, j) : q_infinity());
+    }
+    acc = quads_sum(acc, sh);
+    if (g == 0) q_store(big.part, it, acc);
+  }
+}
+
+// The listed buckets from their items' sums.
+__global__ void __launch_bounds__(kBigThreads) big_bucket_kernel(BigLists big, uint32_t* __restrict__ buckets) {
+  __shared__ uint32_t sh[kBigThreads / 4 * kAccWords];
+  const uint32_t n = big.count[0], g = threadIdx.x / 4;
+  for (uint32_t k = blockIdx.x; k < n; k += gridDim.x) {
+    const uint4 b = big.bucket[k];
+    Fq acc = q_infinity();
+    for (uint32_t i = 0; i < b.z; i += kBigThreads / 4) {
+      const bool have = i + g < b.z;
+      if (__any(have)) acc = q_add(acc, have ? q_load(big.part, b.y + i + g) : q_infinity());
+    }
+    acc = quads_sum(acc, sh);
+    if (g == 0) q_store(buckets, b.x, acc);
+  }
 }
 
 // ---------------------------------------------------------------------------
-// Reduction by bits.  Buckets are grouped in chunks of kChunk consecutive
-// indices.  For a bit b at or above the chunk's bits, bit b is the same for
-// every bucket of chunk t (it is bit b - 3 of t), so its share of G_b is the
-// whole chunk sum S_t or nothing: S_t is computed once, for all those bits.
+// Reduction by bits.  A binary tree over the buckets: node i of level l is the
+// sum of buckets i 2^l .. (i + 1) 2^l - 1, and G_l is the sum of the odd nodes
+// of level l.  A workgroup holds 2^levels points (its S list) and, level by
+// level, adds neighbours in every list it has (S, and the odd nodes of the
+// levels below) and starts a list with the odd nodes of this one, so that
+// each level is at most 2^(levels - 1) additions at the same time, one per
+// quad.  It ends with one point per list: S, G_0, .., G_(levels-1).
+constexpr int kTreeThreads = 512;
 
-// S_t = the sum of the buckets of chunk t.  kChunkLanes lanes share a chunk,
-// each adding kChunk / kChunkLanes of its buckets, and a tree in LDS joins
-// their sums: three point additions in sequence instead of seven.  (Having
-// the same lanes also form the low bits' shares, with a different sum per
-// lane, made the rounds divergent and took three times as long.)
-constexpr uint32_t kChunkLanes = 4;
-constexpr uint32_t kChunkThreads = 64;
-
-__global__ void __launch_bounds__(kChunkThreads) chunk_sum_kernel(const uint32_t* __restrict__ buckets, uint32_t nb,
-                                                                  uint32_t* __restrict__ sums) {
-  __shared__ Xyzz sh[kChunkThreads];
-  const uint32_t g = blockIdx.x * kChunkThreads + threadIdx.x;
-  const uint32_t t = g / kChunkLanes, q = g % kChunkLanes;
-  const uint32_t T = (nb + kChunk - 1) / kChunk;
-  constexpr uint32_t per = kChunk / kChunkLanes;
-  Xyzz acc = infinity();
-  if (t < T)
-    for (uint32_t d = t * kChunk + q * per; d < min(nb, t * kChunk + (q + 1) * per); ++d)
-      acc = add(acc, load_xyzz(buckets, d));
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  for (uint32_t half = kChunkLanes / 2; half > 0; half >>= 1) {
-    if (q < half) sh[threadIdx.x] = add(sh[threadIdx.x], sh[threadIdx.x + half]);
+// in: 2^levels points; lists: true for the whole scheme, false for S alone.
+// Returns list t in quad t.
+__device__ __forceinline__ Fq tree_lists(const uint32_t* __restrict__ in, int levels, bool lists, uint32_t* sh) {
+  const uint32_t g = threadIdx.x / 4;
+  if (levels == 0) return g == 0 ? q_load(in, 0) : q_infinity();
+  for (int l = 0; l < levels; ++l) {
+    const uint32_t half = 1u << (levels - l - 1);       // points of a list after this level
+    const uint32_t nlists = lists ? (uint32_t)l + 1u : 1u;
+    const bool mine = g < nlists * half;
+    const uint32_t* src = l == 0 ? in : sh;
+    Fq a = q_infinity(), b = a, s = a;
+    if (mine) {
+      a = q_load(src, 2 * g);  // list g / half, points 2 (g mod half) and the next
+      b = q_load(src, 2 * g + 1);
+    }
+    if (__any(mine)) s = q_add(a, b);
+    __syncthreads();
+    if (mine) {
+      q_store(sh, g, s);
+      if (lists && g < half) q_store(sh, nlists * half + g, b);  // the odd nodes of this level
+    }
     __syncthreads();
   }
-  if (q == 0 && t < T) store_xyzz(sums, t, sh[threadIdx.x]);
+  const uint32_t n = lists ? (uint32_t)levels + 1u : 1u;
+  return g < n ? q_load(sh, g) : q_infinity();
 }
 
-// Level 0: lane (b, u) holds the share of G_b of chunks t = u C .. u C + C - 1
-// (C = kLevel0Chunks): below the chunks' bits, the sum of their buckets with
-// bit b set (at most kChunk / 2 per chunk); above, the sums S_t of the
-// chunks with bit b set.  A workgroup of kLevel0Lanes lanes of one bit sums
-// them by a tree: out[b * ceil(T / (kLevel0Lanes C)) + blockIdx.x].  Two
-// chunks per lane keep one wave per SIMD, where a point addition's latency
-// is shortest.
-__global__ void __launch_bounds__(kLevel0Lanes) bits_level0_kernel(const uint32_t* __restrict__ buckets,
-                                                                   const uint32_t* __restrict__ sums, uint32_t nb,
-                                                                   uint32_t* __restrict__ out) {
-  __shared__ Xyzz sh[kLevel0Lanes];
-  const uint32_t T = (nb + kChunk - 1) / kChunk;
-  const uint32_t b = blockIdx.y, u = blockIdx.x * kLevel0Lanes + threadIdx.x;
-  Xyzz acc = infinity();
-  for (uint32_t t = u * kLevel0Chunks; t < min(T, (u + 1) * kLevel0Chunks); ++t) {
-    if ((1u << b) < kChunk) {
-      for (uint32_t d = t * kChunk; d < min(nb, (t + 1) * kChunk); ++d)
-        if ((d >> b) & 1u) acc = add(acc, load_xyzz(buckets, d));
-    } else if (((t * kChunk) >> b) & 1u) {
-      acc = add(acc, load_xyzz(sums, t));
-    }
+// Workgroup k: 2^levels buckets from k 2^levels; list t's result to
+// out[t nblk + k] (t = 0: S, 1 + b: G_b).
+__global__ void __launch_bounds__(kTreeThreads) tree_kernel(const uint32_t* __restrict__ buckets, int levels,
+                                                            uint32_t* __restrict__ out) {
+  __shared__ uint32_t sh[2 * (kTreeThreads / 4) * kAccWords];
+  const uint32_t g = threadIdx.x / 4;
+  const Fq r = tree_lists(buckets + ((uint64_t)blockIdx.x << levels) * kAccWords, levels, true, sh);
+  if (g <= (uint32_t)levels) q_store(out, (uint64_t)g * gridDim.x + blockIdx.x, r);
+}
+
+// The workgroups' results, 2^levels per list: workgroup t > 0 sums list t
+// into G_(t-1); workgroup 0 runs the scheme on the S list, whose bits are
+// those above the first kernel's `below`.
+__global__ void __launch_bounds__(kTreeThreads) tree_top_kernel(const uint32_t* __restrict__ in, int levels, int below,
+                                                                uint32_t* __restrict__ G) {
+  __shared__ uint32_t sh[2 * (kTreeThreads / 4) * kAccWords];
+  const uint32_t g = threadIdx.x / 4, t = blockIdx.x;
+  const Fq r = tree_lists(in + ((uint64_t)t << levels) * kAccWords, levels, t == 0, sh);
+  if (t > 0) {
+    if (g == 0) q_store(G, t - 1, r);
+  } else if (g >= 1 && g <= (uint32_t)levels) {
+    q_store(G, (uint64_t)below + g - 1, r);
   }
-  const Xyzz total = lds_tree_sum(acc, sh);
-  if (threadIdx.x == 0) store_xyzz(out, (uint64_t)b * gridDim.x + blockIdx.x, total);
 }
 
-// G_b for b = blockIdx.x: the sum of the `len` level-0 results of bit b,
-// kReduceThreads lanes each summing a strided share, then a tree.
-constexpr int kReduceThreads = 64;  // one wave: at most 2^16 / (8 * 128) = 64 level-0 results per bit
-__global__ void __launch_bounds__(kReduceThreads) reduce_bit_kernel(const uint32_t* __restrict__ in, uint32_t len,
-                                                                    uint32_t* __restrict__ out) {
-  __shared__ Xyzz sh[kReduceThreads];
-  const uint32_t b = blockIdx.x;
-  Xyzz acc = infinity();
-  for (uint32_t k = threadIdx.x; k < len; k += blockDim.x) acc = add(acc, load_xyzz(in, (uint64_t)b * len + k));
-  const Xyzz total = lds_tree_sum(acc, sh);
-  if (threadIdx.x == 0) store_xyzz(out, b, total);
-}
-
-// result = sum_b 2^b G_b (b < c <= 16): lane b doubles G_b b times, then a
+// result = sum_b 2^b G_b (b < c <= 16): quad b doubles G_b b times, then a
 // tree sums the c scaled points.
-__global__ void __launch_bounds__(16) final_kernel(const uint32_t* __restrict__ G, int c, uint32_t* __restrict__ res) {
-  __shared__ Xyzz sh[16];
-  const int b = (int)threadIdx.x;
-  Xyzz p = infinity();
-  if (b < c) {
-    p = load_xyzz(G, (uint64_t)b);
-    for (int k = 0; k < b; ++k) p = dbl(p);
+__global__ void __launch_bounds__(64) final_kernel(const uint32_t* __restrict__ G, int c, uint32_t* __restrict__ res) {
+  __shared__ uint32_t sh[16 * kAccWords];
+  const int b = (int)threadIdx.x / 4;
+  Fq p = b < c ? q_load(G, (uint64_t)b) : q_infinity();
+#pragma unroll 1
+  for (int k = 0; k + 1 < c; ++k) {
+    const Fq two = q_dbl(p);
+    p = sel(k < b && b < c, two, p);
   }
-  Xyzz total = lds_tree_sum(p, sh);
-  if (threadIdx.x == 0) {
-    // the result leaves the device canonical
-    total.X = fq::canon(total.X);
-    total.Y = fq::canon(total.Y);
-    total.ZZ = fq::canon(total.ZZ);
-    total.ZZZ = fq::canon(total.ZZZ);
-    store_xyzz(res, 0, total);
+  p = quads_sum(p, sh);
+  if (b == 0) {
+    // the result leaves the device canonical, in Montgomery form 2^384
+    uint32_t w[fq::kWords];
+    fq::pack_canonical(w, fq::mul(p, fq::constant(fq::kTo384)));
+#pragma unroll
+    for (int k = 0; k < fq::kWords; ++k) res[fq::kWords * quad_lane() + k] = w[k];
   }
 }
 
@@ -678,7 +795,7 @@ hipError_t launch_msm(const MsmLaunch& m, hipStream_t s) {
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(column_scan_kernel, dim3(blocks(nb, 256)), dim3(256), 0, s, m.hist, nb, m.groups, m.counts);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, s, m.counts, nb, m.offsets, m.big_count);
+  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, s, m.counts, nb, m.offsets, m.big.count);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(scatter_kernel, dim3(blocks(m.n, 256) * (uint32_t)m.windows), dim3(256), 0, s, m.digits,
                      m.ranks, m.n, m.windows, m.per_group, nb, m.hist, m.offsets, m.entries);
@@ -688,25 +805,23 @@ hipError_t launch_msm(const MsmLaunch& m, hipStream_t s) {
   hipLaunchKernelGGL(accumulate_kernel, dim3(blocks(m.lanes, kAccumulateThreads)), dim3(kAccumulateThreads), 0, s,
                      m.table, m.entries, m.offsets, nb, m.lanes, m.kmin, m.head, m.tail, m.buckets);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(combine_kernel, dim3(blocks(nb, 128)), dim3(128), 0, s, m.offsets, nb, m.lanes, m.kmin, m.head,
-                     m.tail, m.buckets, m.big, m.big_count);
+  hipLaunchKernelGGL(combine_kernel, dim3(blocks((uint64_t)nb * 4, 256)), dim3(256), 0, s, m.offsets, nb, m.lanes,
+                     m.kmin, m.head, m.tail, m.buckets, m.big);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(big_combine_kernel, dim3(max_big_buckets(m.lanes)), dim3(kBigThreads), 0, s, m.offsets, nb,
-                     m.lanes, m.kmin, m.head, m.tail, m.big, m.big_count, m.buckets);
+  const uint32_t item_blocks = std::min<uint32_t>(max_big_items(m.lanes), 512u);
+  hipLaunchKernelGGL(big_item_kernel, dim3(item_blocks), dim3(kBigThreads), 0, s, m.offsets, nb, m.lanes, m.kmin,
+                     m.head, m.tail, m.big);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(big_bucket_kernel, dim3(std::min<uint32_t>(max_big_buckets(m.lanes), 512u)), dim3(kBigThreads), 0,
+                     s, m.big, m.buckets);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // reduction by bits
-  const uint32_t T = (nb + kChunk - 1) / kChunk;
-  hipLaunchKernelGGL(chunk_sum_kernel, dim3(blocks((uint64_t)T * kChunkLanes, kChunkThreads)), dim3(kChunkThreads), 0,
-                     s, m.buckets, nb, m.chunk_sums);
+  const int low = std::min(m.c, kTreeLevels);
+  hipLaunchKernelGGL(tree_kernel, dim3(1u << (m.c - low)), dim3(kTreeThreads), 0, s, m.buckets, low, m.level_a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const uint32_t T0 = blocks(T, kLevel0Lanes * kLevel0Chunks);  // level-0 results per bit
-  hipLaunchKernelGGL(bits_level0_kernel, dim3(T0, m.c), dim3(kLevel0Lanes), 0, s, m.buckets, m.chunk_sums, nb,
-                     m.level_a);
+  hipLaunchKernelGGL(tree_top_kernel, dim3(1 + low), dim3(kTreeThreads), 0, s, m.level_a, m.c - low, low, m.level_b);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  // each bit's level-0 results into G_b, then sum_b 2^b G_b
-  hipLaunchKernelGGL(reduce_bit_kernel, dim3(m.c), dim3(kReduceThreads), 0, s, m.level_a, T0, m.level_b);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(final_kernel, dim3(1), dim3(16), 0, s, m.level_b, m.c, m.result);
+  hipLaunchKernelGGL(final_kernel, dim3(1), dim3(64), 0, s, m.level_b, m.c, m.result);
   return hipGetLastError();
 }
 

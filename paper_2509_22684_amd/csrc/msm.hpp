@@ -6,11 +6,20 @@
 namespace zk {
 namespace msm {
 
-constexpr int kPointWords = 24;  // affine point: x, y as 12 limbs each
-constexpr int kXyzzWords = 48;   // X, Y, ZZ, ZZZ
-constexpr uint32_t kChunk = 8;         // buckets per chunk in the reduction by bits
-constexpr uint32_t kLevel0Lanes = 64;  // level-0 lanes summed per result in the reduction by bits
-constexpr uint32_t kLevel0Chunks = 2;  // chunks per level-0 lane
+constexpr int kPointWords = 24;  // affine point: x, y as twelve 32-bit words each
+constexpr int kXyzzWords = 48;   // the result: X, Y, ZZ, ZZZ, twelve words each
+constexpr int kAccWords = 56;    // a working point: X, Y, ZZ, ZZZ, fourteen limbs each
+constexpr int kScratchWords = kAccWords + 14;  // precomputation, per window: a point and a prefix product
+constexpr int kTreeLevels = 8;   // levels of the bucket tree in one workgroup
+
+// Buckets that span many runs, and the items their sums are cut into.
+constexpr uint32_t kBigRuns = 128;  // runs per item
+struct BigLists {
+  uint32_t* count;   // buckets listed, items listed
+  uint4* bucket;     // max_big_buckets(lanes): bucket, first item, items
+  uint32_t* item;    // max_big_items(lanes): index into bucket
+  uint32_t* part;    // max_big_items(lanes) working points
+};
 
 // Everything one MSM launch touches; the buffers are slices of the caller's
 // workspace (sizes in msm_workspace_bytes).
@@ -30,26 +39,26 @@ struct MsmLaunch {
   uint32_t* counts;         // 2^c
   uint32_t* offsets;        // 2^c + 1
   uint32_t* entries;        // windows x n
-  uint32_t* head;           // lanes XYZZ
-  uint32_t* tail;           // lanes XYZZ
-  uint32_t* big;            // max_big_buckets(lanes) bucket indices
-  uint32_t* big_count;      // one word
-  uint32_t* buckets;        // 2^c XYZZ
-  uint32_t* chunk_sums;     // ceil(2^c / kChunk) XYZZ
-  uint32_t* level_a;        // c x ceil(ceil(2^c / kChunk) / (kLevel0Lanes kLevel0Chunks)) XYZZ
-  uint32_t* level_b;        // c XYZZ
+  uint32_t* head;           // lanes working points
+  uint32_t* tail;           // lanes working points
+  BigLists big;
+  uint32_t* buckets;        // 2^c working points
+  uint32_t* level_a;        // (1 + min(c, kTreeLevels)) x 2^(c - min(c, kTreeLevels)) working points
+  uint32_t* level_b;        // c working points
   uint32_t* result;         // one XYZZ point
 };
 
 // table[w n + i] = 2^(c w) P_i for points first .. first + count of n;
-// scratch: count x windows x 60 words.
+// scratch: count x windows x kScratchWords words.
 hipError_t launch_precompute(const uint32_t* pts, uint64_t n, uint64_t first, uint64_t count, int c, int windows,
                              uint32_t* table, uint32_t* scratch, hipStream_t s);
-// A combine lane adds at most kCombineSerial runs' heads; a bucket spanning
-// more runs is listed for a workgroup.  Such buckets own more than
-// kCombineSerial run starts each, so at most lanes / kCombineSerial + 1.
+// A combine quad adds at most kCombineSerial runs' heads; a bucket spanning
+// more runs is listed.  Such buckets own more than kCombineSerial run starts
+// each, so at most lanes / kCombineSerial + 1 of them, and each has one item
+// per kBigRuns run starts, rounded up.
 constexpr uint32_t kCombineSerial = 16;
 inline uint32_t max_big_buckets(uint32_t lanes) { return lanes / kCombineSerial + 1u; }
+inline uint32_t max_big_items(uint32_t lanes) { return lanes / kBigRuns + max_big_buckets(lanes); }
 
 // Accumulation lanes that are resident on the current device at once.
 hipError_t accumulate_lanes(uint32_t* lanes);
