@@ -104,6 +104,17 @@ __device__ __forceinline__ Fq constant(const Limbs& c) {
 __device__ __forceinline__ Fq zero() { return constant(Limbs{}); }
 __device__ __forceinline__ Fq one() { return constant(kOne); }
 
+// Hides how a's limbs were computed.  A limb whose sign extension or negation
+// the compiler has already formed, in another block or as a 64-bit value,
+// enters a product as a 64-bit operand: four instructions instead of one.
+__device__ __forceinline__ Fq opaque(Fq a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+  for (int i = 0; i < kN; ++i) asm("" : "+v"(a.v[i]));
+#endif
+  return a;
+}
+
 // Limb by limb, no carries.
 __device__ __forceinline__ Fq add(const Fq& a, const Fq& b) {
   Fq r;
@@ -121,7 +132,7 @@ __device__ __forceinline__ Fq neg(const Fq& a) {
   Fq r;
 #pragma unroll
   for (int i = 0; i < kN; ++i) r.v[i] = -a.v[i];
-  return r;
+  return opaque(r);
 }
 __device__ __forceinline__ Fq dbl(const Fq& a) { return add(a, a); }
 
@@ -164,6 +175,8 @@ __device__ __forceinline__ bool is_zero(const Fq& a) {
   return o == 0;
 }
 
+__device__ __forceinline__ int64_t mad(int32_t a, int32_t b, int64_t acc) { return acc + (int64_t)a * b; }
+
 // (sum of products - m q) / 2^392, column by column; col(i, acc) adds column
 // i of the products to the accumulator.
 template <class Col>
@@ -175,16 +188,16 @@ __device__ __forceinline__ Fq reduce(Col col) {
   for (int i = 0; i < kN; ++i) {
     acc = col(i, acc);
 #pragma unroll
-    for (int j = 0; j < i; ++j) acc += (int64_t)m[j] * -kQ28.v[i - j];
+    for (int j = 0; j < i; ++j) acc = mad(m[j], -kQ28.v[i - j], acc);
     m[i] = (int32_t)(((uint32_t)acc * kInv) & kMask);
-    acc += (int64_t)m[i] * -kQ28.v[0];
+    acc = mad(m[i], -kQ28.v[0], acc);
     acc >>= kBits;
   }
 #pragma unroll
   for (int i = kN; i < 2 * kN - 1; ++i) {
     acc = col(i, acc);
 #pragma unroll
-    for (int j = i - (kN - 1); j < kN; ++j) acc += (int64_t)m[j] * -kQ28.v[i - j];
+    for (int j = i - (kN - 1); j < kN; ++j) acc = mad(m[j], -kQ28.v[i - j], acc);
     r.v[i - kN] = (int32_t)((uint32_t)acc & kMask);
     acc >>= kBits;
   }
@@ -195,7 +208,7 @@ __device__ __forceinline__ Fq reduce(Col col) {
 __device__ __forceinline__ int64_t column(const Fq& a, const Fq& b, int i, int64_t acc) {
 #pragma unroll
   for (int j = 0; j < kN; ++j)
-    if (j <= i && i - j < kN) acc += (int64_t)a.v[j] * b.v[i - j];
+    if (j <= i && i - j < kN) acc = mad(a.v[j], b.v[i - j], acc);
   return acc;
 }
 
@@ -209,12 +222,12 @@ __device__ __forceinline__ Fq mul_add(const Fq& a, const Fq& b, const Fq& c, con
 }
 
 __device__ __forceinline__ Fq sqr(const Fq& a) {
-  const Fq t = dbl(a);
+  const Fq t = opaque(dbl(a));
   return reduce([&](int i, int64_t acc) {
 #pragma unroll
     for (int j = 0; j < kN; ++j) {
-      if (2 * j < i && i - j < kN) acc += (int64_t)t.v[j] * a.v[i - j];
-      if (2 * j == i) acc += (int64_t)a.v[j] * a.v[j];
+      if (2 * j < i && i - j < kN) acc = mad(t.v[j], a.v[i - j], acc);
+      if (2 * j == i) acc = mad(a.v[j], a.v[j], acc);
     }
     return acc;
   });

@@ -113,12 +113,13 @@ __device__ __forceinline__ Xyzz dbl_affine(const Affine& a) {
 // ZZZ3 = ZZZ1 PPP.  P = 0 means x-coordinates agree: the points are equal
 // (double A) or opposite (`cancelled`: infinity).
 __device__ __forceinline__ Xyzz add_mixed(const Xyzz& p, const Affine& a, bool& cancelled) {
-  const Fq P = fq::sub(fq::mul(a.x, p.ZZ), p.X);
+  Fq P = fq::sub(fq::mul(a.x, p.ZZ), p.X);
   const Fq R = fq::sub(fq::mul(a.y, p.ZZZ), p.Y);
   if (fq::is_zero(P)) {
     cancelled = !fq::is_zero(R);
     return cancelled ? infinity() : dbl_affine(a);
   }
+  P = fq::opaque(P);  // is_zero has its limbs' 64-bit extensions
   const Fq PP = fq::sqr(P);
   const Fq PPP = fq::mul(P, PP), Q = fq::mul(p.X, PP);
   Xyzz r;
