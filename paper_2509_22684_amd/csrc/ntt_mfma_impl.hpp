@@ -34,10 +34,6 @@ using detail::sfor;
 using detail::store_fe;
 using detail::U32x4;
 
-#ifndef MAX_WAVES
-#define MAX_WAVES 4
-#endif
-
 // The rounds of a radix-2^LOG_R pass, most significant digit first.  A round
 // of radix rho takes its columns 32 at a time, so a tile of 2^LOG_TILE
 // elements needs 2^LOG_TILE / rho >= 32.
@@ -80,7 +76,7 @@ struct Shape {
   static constexpr int LDS_A = 16 * 64;    // the matrices
   static constexpr int LDS_WGS = 163840 / (16 * (LDS_DATA + LDS_A));
   static constexpr int WAVES_SIMD = LDS_WGS * THREADS / 256;
-  static constexpr int MIN_WAVES = WAVES_SIMD < 1 ? 1 : WAVES_SIMD > MAX_WAVES ? MAX_WAVES : WAVES_SIMD;
+  static constexpr int MIN_WAVES = WAVES_SIMD < 1 ? 1 : WAVES_SIMD > 4 ? 4 : WAVES_SIMD;
 };
 
 // 16-byte slot of half h of element e: within each 256-byte row the halves
@@ -135,12 +131,6 @@ __device__ __forceinline__ int64_t mad_i64(int32_t a, int32_t b, int64_t c) {
   asm("v_mad_i64_i32 %0, %1, %2, %3, %4" : "=v"(r), "=s"(unused) : "v"(a), "s"(b), "v"(c));
   return r;
 }
-__device__ __forceinline__ int64_t add_i64(int32_t a, int64_t c) {
-  int64_t r;
-  uint64_t unused;
-  asm("v_mad_i64_i32 %0, %1, %2, 1, %3" : "=v"(r), "=s"(unused) : "v"(a), "v"(c));
-  return r;
-}
 __device__ __forceinline__ V16i mfma(V4i a, V4i b, V16i c) {
   return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
 }
@@ -151,14 +141,13 @@ __device__ __forceinline__ void swap_halves(int& x, int& y) {
 }
 #else
 inline __device__ int64_t mad_i64(int32_t a, int32_t b, int64_t c) { return (int64_t)a * b + c; }
-inline __device__ int64_t add_i64(int32_t a, int64_t c) { return a + c; }
 inline __device__ V16i mfma(V4i, V4i, V16i c) { return c; }
 inline __device__ void swap_halves(int&, int&) {}
 #endif
 
 // The element with byte-pair columns u_l + 2^16 v_l at limb l (each below
-// 2^31 in magnitude: a radix-16 column is at most 2^7 times the digit sum of a
-// matrix row, below 2^22.01, and 2^22.01 (1 + 2^8) < 2^31; checked against
+// 2^30.1 in magnitude: a radix-16 column is at most 2^7 times the digit sum of
+// a matrix row, below 2^22.01, and 2^22.01 (1 + 2^8) < 2^30.1; checked against
 // the tables by the tests), reduced to [0, 1.3 p) below 2^256.  The multiple
 // of p comes from the top limb's columns in single precision: they carry the
 // quotient (at most 2^18.1 in magnitude) to within 2^-5, and rounding down
@@ -169,16 +158,24 @@ __device__ __forceinline__ Fe combine(const int (&u)[8], const int (&v)[8]) {
   const float t = __builtin_fmaf((float)v[7], 65536.0f, (float)u[7]);
   const int nq = -(int)__builtin_floorf(__builtin_fmaf(t, inv_top<F>(), -0.125f));
   Fe r;
-  int64_t acc = 0;
+  int32_t carry = 0;  // below 2^18.2 in magnitude, so u_l + carry fits 32 bits
   sfor<8>([&](auto l_) {
     constexpr int l = decltype(l_)::value;
-    acc = add_i64(u[l], acc);
-    acc = mad_i64(v[l], 65536, acc);
-    acc = mad_i64(nq, pb.v[l], acc);
+    const int64_t acc = mad_i64(nq, pb.v[l], mad_i64(v[l], 65536, (int64_t)(u[l] + carry)));
     r.v[l] = (uint32_t)acc;
-    acc >>= 32;
+    carry = (int32_t)(acc >> 32);
   });
   return r;
+}
+
+// Digit value at which output i of a radix-2^LOG_RHO round is stored, and back.
+template <bool HALF, int LOG_RHO>
+__device__ __forceinline__ uint32_t out_digit(uint32_t i) {
+  return HALF ? (i >> 1) | ((i & 1u) << (LOG_RHO - 1)) : i;
+}
+template <bool HALF, int LOG_RHO>
+__device__ __forceinline__ uint32_t digit_out(uint32_t d) {
+  return HALF ? ((d << 1) & ((1u << LOG_RHO) - 1)) | (d >> (LOG_RHO - 1)) : d;
 }
 
 // One pair of accumulator tiles (outputs i0 and i1 of 32 columns): lane
@@ -219,7 +216,9 @@ __device__ __forceinline__ V4i lds_half(const U32x4* lds, uint32_t slot) {
 //
 // HALF: digit values j < rho/2 hold x_j + x_(j + rho/2), the others
 // x_j - x_(j + rho/2).  Even outputs sum over the former, odd ones over the
-// latter, rho/2 terms each; a group is 32 columns and one parity.
+// latter, rho/2 terms each; a group is 32 columns and one parity.  Output i
+// goes to digit value out_digit(i), among the group's own inputs, so that a
+// wave that owns a group needs no other wave's agreement to write.
 template <class F, int LOG_R, int LOG_TILE, int LOG_THREADS, int Q>
 __device__ __forceinline__ void dft_round(U32x4* lds) {
   using S = Shape<LOG_R, LOG_TILE, LOG_THREADS>;
@@ -242,10 +241,9 @@ __device__ __forceinline__ void dft_round(U32x4* lds) {
   };
   constexpr int PER = S::U < PAIRS ? S::U : PAIRS;  // pairs of a group taken by one wave
   constexpr int GROUPS = S::U / PER;                // groups per wave
-  constexpr bool SHARED = PER < PAIRS || S::HALF;   // other waves read this wave's outputs' slots
-  constexpr int G = PER >= 2 ? 2 : 1;               // pairs in flight
-  Fe out[S::U];
-  uint32_t where[GROUPS];
+  constexpr bool SHARED = PER < PAIRS;              // other waves read the slots this wave writes
+  constexpr int G = PER >= 2 ? 2 : PER;             // pairs in flight
+  Fe out[SHARED ? PER : G];
   sfor<GROUPS>([&](auto k_) {
     constexpr int k = decltype(k_)::value;
     const uint32_t unit = (wave * GROUPS + k) * PER;
@@ -253,37 +251,49 @@ __device__ __forceinline__ void dft_round(U32x4* lds) {
     const uint32_t parity = S::HALF ? group & 1u : 0u, nt = S::HALF ? group >> 1 : group;
     const uint32_t e0 = base(nt);
     const uint32_t in0 = slot_at<SH>(slot16(e0, h), parity * TERMS);
+    // output i0 + h of pair p: digit value parity TERMS + 2 p + h
+    const uint32_t out0 = slot_at<SH>(slot16(e0, 0), parity * TERMS + 2 * pair0 + h);
     V4i b[TERMS];
     sfor<TERMS>([&](auto j_) {
       constexpr int j = decltype(j_)::value;
       b[j] = lds_half(lds, slot_at<SH>(in0, j));
     });
+    // Term 0's factor is w^0 = 1 for every output: its digits start the
+    // accumulators (rows 8 g + 4 h + q are byte q of limb g + 4 h, which is
+    // word g of this lane's half).
+    V16i first_term;
+    sfor<16>([&](auto r_) {
+      constexpr int r = decltype(r_)::value;
+      first_term[r] = (int)((unsigned)b[0][r / 4] << (24 - 8 * (r % 4))) >> 24;
+    });
     sfor<PER / G>([&](auto g_) {
       constexpr int g = decltype(g_)::value;
       V16i acc[2 * G];
-      sfor<2 * G>([&](auto t_) { sfor<16>([&](auto x_) { acc[decltype(t_)::value][decltype(x_)::value] = 0; }); });
-      sfor<TERMS>([&](auto j_) {
-        constexpr int j = decltype(j_)::value;
+      sfor<2 * G>([&](auto t_) { acc[decltype(t_)::value] = first_term; });
+      sfor<TERMS - 1>([&](auto j_) {
+        constexpr int j = decltype(j_)::value + 1;
         sfor<2 * G>([&](auto t_) {
           constexpr int t = decltype(t_)::value;
-          const uint32_t i = S::HALF ? 2 * (2 * (pair0 + G * g + t / 2) + t % 2) + parity
-                                     : 2 * (pair0 + G * g + t / 2) + t % 2;
+          const uint32_t m = 2 * (pair0 + G * g + t / 2) + t % 2;
+          const uint32_t i = S::HALF ? 2 * m + parity : m;
           acc[t] = mfma(amat[((i * j * STEP) & 15u) * 64u], b[j], acc[t]);
         });
       });
       sfor<G>([&](auto p_) {
         constexpr int p = decltype(p_)::value;
-        out[k * PER + G * g + p] =
-            finish<F, TERMS>(acc[2 * p], acc[2 * p + 1], parity == 0 && pair0 + G * g + p == 0);
+        const Fe x = finish<F, TERMS>(acc[2 * p], acc[2 * p + 1], parity == 0 && pair0 + G * g + p == 0);
+        if constexpr (SHARED) out[G * g + p] = x;
+        else lds_store(lds, slot_at<SH>(out0, 2 * (G * g + p)), x, 0u);
       });
     });
-    // slot of this lane's first output; the pairs' are 4 (HALF) or 2 digit values apart
-    where[k] = S::HALF ? slot_at<SH>(slot16(e0, 0), 4 * pair0 + 2 * h + parity) : slot_at<SH>(slot16(e0, 0), 2 * pair0 + h);
-  });
-  if constexpr (SHARED) __syncthreads();  // every wave has read its inputs
-  sfor<S::U>([&](auto u_) {
-    constexpr int u = decltype(u_)::value;
-    lds_store(lds, slot_at<SH>(where[u / PER], (S::HALF ? 4 : 2) * (u % PER)), out[u], 0u);
+    if constexpr (SHARED) {
+      static_assert(GROUPS == 1, "a shared group is a wave's only one");
+      __syncthreads();  // every wave has read its inputs
+      sfor<PER>([&](auto u_) {
+        constexpr int u = decltype(u_)::value;
+        lds_store(lds, slot_at<SH>(out0, 2 * u), out[u], 0u);
+      });
+    }
   });
 }
 
@@ -361,7 +371,8 @@ __device__ __forceinline__ void rounds(U32x4* lds, const Fe* __restrict__ tw_r) 
         constexpr int k = decltype(k_)::value;
         const uint32_t e = S::HALF ? elem_at<P, S::THREADS>(it + k) : threadIdx.x;
         const uint32_t r = e >> S::LOG_J;
-        const uint32_t low = r & ((1u << LOG_LOW) - 1), i = (r >> LOG_LOW) & (RHO - 1);
+        const uint32_t low = r & ((1u << LOG_LOW) - 1);
+        const uint32_t i = digit_out<S::HALF, Rd::log(Q)>((r >> LOG_LOW) & (RHO - 1));
         slot[k] = slot16(e, 0);
         w[k] = load_fe(tw_r, (i * low) << Rd::high(Q));
         x[k] = lds_load(lds, slot[k]);
@@ -454,8 +465,8 @@ __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS)
 
   rounds<F, LOG_R, LOG_TILE, LOG_THREADS, 0>(lds, a.tw_r);
 
-  // store: output k of column c sits at the slot with digits (i_1, i_2, ...)
-  // in place of (r_1, r_2, ...).  The first pass writes J R consecutive
+  // store: output k of column c sits at the slot with the digits of
+  // (i_1, i_2, ...) in place of (r_1, r_2, ...).  The first pass writes J R consecutive
   // elements, output index fastest; later passes write runs of J columns.
   const bool k_fast = a.log_ns == 0;
 #pragma unroll 1
@@ -470,7 +481,7 @@ __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS)
       uint32_t r = 0;
       sfor<Rd::N>([&](auto d_) {
         constexpr int d = decltype(d_)::value;
-        r |= ((k >> Rd::high(d)) & ((1u << Rd::log(d)) - 1)) << Rd::low(d);
+        r |= out_digit<S::HALF, Rd::log(d)>((k >> Rd::high(d)) & ((1u << Rd::log(d)) - 1)) << Rd::low(d);
       });
       x[q] = lds_load(lds, slot16((r << S::LOG_J) + c, 0));
       const uint64_t j = j0 + c;
