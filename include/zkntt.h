@@ -74,12 +74,13 @@ typedef struct {
   uint32_t twiddle_mode;    /* 0 default; 1 one precomputed table per pass in HBM;
                                2 two small tables and one extra multiplication per element */
   uint32_t log2_radix;      /* radix of the in-register butterflies: 0 default (1, radix-2, up to
-                               n = 2^18; 2 above), 1 (radix-2), 2 or 3 */
-  uint32_t log2_tile;       /* elements per workgroup tile of a multi-pass transform, log2:
-                               0 default (8 for radix-2 transforms of n = 2^10 .. 2^16,
-                               else 10); 8 (small transforms over more CUs; register
-                               radix 2 or 4 only, passes of at most 2^7 points); 10; or
-                               11 (twice the LDS, half the workgroups per CU) */
+                               n = 2^18; 2 above), 1 (radix-2), 2 or 3.  Read for the FP64
+                               product (2); the other passes' rounds run on the matrix cores */
+  uint32_t log2_tile;       /* the largest transform run in one pass, log2: 0 default (8 for
+                               radix-2 transforms of n = 2^10 .. 2^16, else 10), 8, 10 or 11;
+                               for the FP64 product also the elements per workgroup tile of a
+                               multi-pass transform (8: register radix 2 or 4 only, passes of
+                               at most 2^7 points) */
   uint32_t flags;           /* ZK_FLAG_* */
   uint32_t log2_pass_radix; /* most butterfly stages fused into one global pass: 0 default (9 up to
                                n = 2^18, so at most two passes there; 8 above), 4..9 */
@@ -158,8 +159,8 @@ int ntt_coset_forward(const ntt_plan *p, const void *d_in, void *d_out, void *d_
 int ntt_coset_inverse(const ntt_plan *p, const void *d_in, void *d_out, void *d_work, void *stream);
 
 /* Bytes of device workspace quotient_poly needs (up to n = 2^22 it holds
- * three transform workspaces, so that A's and B's transforms can run at the
- * same time as C's). */
+ * three transform workspaces, so that A's, B's and C's transforms can run at
+ * the same time). */
 size_t quotient_workspace_bytes(const ntt_plan *p);
 
 /* Groth16 quotient chain (Section II, Fig. 3; seven NTTs, Section IV-A).
@@ -171,10 +172,8 @@ size_t quotient_workspace_bytes(const ntt_plan *p);
  *   H = cosetINTT( (cosetNTT(INTT A) . cosetNTT(INTT B) - cosetNTT(INTT C)) / (g^n - 1) ).
  * A, B, C are not modified; H must not overlap them or d_work, and d_work
  * must not overlap A, B or C (ZK_EINVAL; the byte ranges are compared).
- * Up to n = 2^22 the transforms of A and B run on two streams of the plan,
- * forked from `stream` and joined back into it before C's forward NTT, so
- * the call still completes in the order of `stream`; calls on one plan from
- * several threads are serialised while they enqueue. */
+ * Up to n = 2^22 the transforms of A, B and C advance together, each pass one
+ * launch for all three. */
 int quotient_poly(const ntt_plan *p, const void *d_A, const void *d_B, const void *d_C, void *d_H,
                   void *d_work, void *stream);
 
@@ -218,7 +217,7 @@ int zk_copy_to_host(void *host_dst, const void *dev_src, size_t bytes, void *str
  * launch per pass for all jobs of the group) over the whole chip; the choice
  * follows a time estimate made when the batch is created.  A pointwise job
  * larger than an eighth of the batch runs as its own launch the same way.
- * Such launches go to up to three side streams of the batch, forked from the
+ * Such launches go to up to four side streams of the batch, forked from the
  * launch stream before the persistent kernel and joined into it after (in
  * the graph: parallel branches), so the call still completes in stream
  * order on the stream it was given.

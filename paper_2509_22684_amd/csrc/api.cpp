@@ -92,12 +92,6 @@ struct ntt_plan {
   Fe* inv_to_coset = nullptr;     // n^-1 g^k
   uint32_t* d_count = nullptr;    // validation counter
   std::mutex validate_mu;
-  // quotient_poly up to 2^kQuotientForkMaxLog: A's and B's chains run on two
-  // side streams forked from the caller's stream and joined back
-  hipStream_t qside[2] = {nullptr, nullptr};
-  hipEvent_t qfork = nullptr;
-  hipEvent_t qjoin[2] = {nullptr, nullptr};
-  std::mutex quotient_mu;  // one fork/join sequence at a time per plan
   ntt_plan_opts opts{};    // the resolved schedule
 };
 
@@ -169,18 +163,19 @@ struct TableBuilder {
 
 void free_plan(ntt_plan* p) {
   if (!p) return;
-  for (int i = 0; i < 2; ++i) {
-    if (p->qside[i]) (void)hipStreamDestroy(p->qside[i]);
-    if (p->qjoin[i]) (void)hipEventDestroy(p->qjoin[i]);
-  }
-  if (p->qfork) (void)hipEventDestroy(p->qfork);
   for (void* d : p->owned) (void)hipFree(d);
   delete p;
 }
 
-// Plans whose quotient chain runs A's and B's transforms on side streams.
-constexpr uint32_t kQuotientForkMaxLog = 22;
-bool quotient_forks(const ntt_plan* p) { return p->log_n <= kQuotientForkMaxLog; }
+// Up to 2^22 one transform does not fill the chip, or leaves a large part of
+// its last round of workgroups empty, and the quotient chain advances A, B and
+// C together, each pass one launch for all three, with a transform workspace
+// each.  Against A's and B's chains on two side streams beside C's: 2^14 55
+// and 112 us, 2^18 220 and 290, 2^19 407 and 377 to 420, 2^21 1470 and 1545,
+// 2^22 2.92 and 2.89 ms (there the streams' overlap depends on the hardware
+// queues they fall on).
+constexpr uint32_t kQuotientGroupMaxLog = 22;
+bool quotient_groups(const ntt_plan* p) { return p->log_n <= kQuotientGroupMaxLog; }
 
 // Split log_n into passes of at most max_log_r stages each, larger radices
 // first (a single pass covers n up to the tile size in one tile).  A column
@@ -487,26 +482,45 @@ int run_transform(const ntt_plan* p, Kind kind, const void* in, void* out, void*
   return ZK_OK;
 }
 
-size_t workspace_elems(const ntt_plan* p) { return p->passes.size() >= 2 ? p->n : 0; }
-
-// Forward NTT of `in` whose last pass also applies the quotient's pointwise
-// step with the coset evaluations a and b: out = (a b - NTT(in)) / (g^n - 1).
-int run_forward_pointwise(const ntt_plan* p, const void* in, void* out, void* work, const Fe* a, const Fe* b,
-                          hipStream_t s) {
-  const size_t P = p->passes.size();
-  for (size_t k = 0; k < P; ++k) {
+// Passes first .. end - 1 of `jobs` (at most kMaxFew) transforms of one kind, a
+// launch per pass for all of them.
+struct Vectors {
+  const void* in;
+  void* out;
+  void* work;
+};
+int run_grouped(const ntt_plan* p, Kind kind, const Vectors* v, uint32_t jobs, size_t first, size_t end, hipStream_t s) {
+  for (size_t k = first; k < end; ++k) {
     const PassDesc& d = p->passes[k];
-    zk::PassArgs args = make_pass_args(p, kForwardShifted, k, in, out, work);
-    if (k + 1 == P) {
-      args.flags |= zk::kPassPostPointwise;
-      args.pw_a = a;
-      args.pw_b = b;
-      args.post_const = p->zinv;
+    zk::PassArgs a = make_pass_args(p, kind, k, v[0].in, v[0].out, v[0].work);
+    a.grp_jobs = jobs;
+    for (uint32_t j = 1; j < jobs; ++j) {
+      const zk::PassArgs b = make_pass_args(p, kind, k, v[j].in, v[j].out, v[j].work);
+      a.few_in[j - 1] = b.in;
+      a.few_out[j - 1] = b.out;
     }
-    hipError_t e = zk::launch_pass(p->field, d.log_r, d.log_tile, args, s);
-    if (e != hipSuccess) return hip_fail(e, "NTT pass launch");
+    hipError_t e = zk::launch_pass(p->kfield, d.log_r, d.log_tile, a, s);
+    if (e != hipSuccess) return hip_fail(e, "grouped NTT pass launch");
   }
   return ZK_OK;
+}
+
+size_t workspace_elems(const ntt_plan* p) { return p->passes.size() >= 2 ? p->n : 0; }
+
+// The last pass of a forward NTT of `in` that also applies the quotient's
+// pointwise step with the coset evaluations a and b:
+// out = (a b - NTT(in)) / (g^n - 1).
+int run_last_pointwise(const ntt_plan* p, const void* in, void* out, void* work, const Fe* a, const Fe* b,
+                       hipStream_t s) {
+  const size_t k = p->passes.size() - 1;
+  const PassDesc& d = p->passes[k];
+  zk::PassArgs args = make_pass_args(p, kForwardShifted, k, in, out, work);
+  args.flags |= zk::kPassPostPointwise;
+  args.pw_a = a;
+  args.pw_b = b;
+  args.post_const = p->zinv;
+  hipError_t e = zk::launch_pass(p->field, d.log_r, d.log_tile, args, s);
+  return e == hipSuccess ? ZK_OK : hip_fail(e, "NTT pass launch");
 }
 
 int transform_entry(const ntt_plan* p, Kind kind, const void* in, void* out, void* work, void* stream) {
@@ -600,17 +614,6 @@ int ntt_plan_create(ntt_plan** out, int field, uint32_t log2n, const ntt_plan_op
   if (rc) {
     free_plan(p);
     return rc;
-  }
-  if (quotient_forks(p)) {
-    e = hipEventCreateWithFlags(&p->qfork, hipEventDisableTiming);
-    for (int i = 0; i < 2 && e == hipSuccess; ++i) {
-      e = hipStreamCreateWithFlags(&p->qside[i], hipStreamNonBlocking);
-      if (e == hipSuccess) e = hipEventCreateWithFlags(&p->qjoin[i], hipEventDisableTiming);
-    }
-    if (e != hipSuccess) {
-      free_plan(p);
-      return hip_fail(e, "quotient side streams");
-    }
   }
   *out = p;
   return ZK_OK;
@@ -710,7 +713,7 @@ int ntt_coset_inverse(const ntt_plan* p, const void* d_in, void* d_out, void* d_
 }
 
 size_t quotient_workspace_bytes(const ntt_plan* p) {
-  return p ? (2 * p->n + (quotient_forks(p) ? 3 : 1) * workspace_elems(p)) * sizeof(Fe) : 0;
+  return p ? (2 * p->n + (quotient_groups(p) ? 3 : 1) * workspace_elems(p)) * sizeof(Fe) : 0;
 }
 
 int quotient_poly(const ntt_plan* p, const void* d_A, const void* d_B, const void* d_C, void* d_H, void* d_work,
@@ -739,33 +742,18 @@ int quotient_poly(const ntt_plan* p, const void* d_A, const void* d_B, const voi
   const size_t ws = workspace_elems(p);
   Fe* w = ws ? t2 + p->n : nullptr;
   Fe* H = static_cast<Fe*>(d_H);
-  if (quotient_forks(p)) {
-    // Up to 2^kQuotientForkMaxLog one transform does not fill the chip: A's
-    // and B's INTT->NTT chains run on two side streams beside C's INTT, each
-    // with its own workspace, and C's forward NTT with the pointwise step
-    // waits for both.  Same kernels and arguments, so the same bytes.
-    std::lock_guard<std::mutex> lock(const_cast<ntt_plan*>(p)->quotient_mu);
-    hipError_t e = hipEventRecord(p->qfork, s);
-    for (int i = 0; i < 2 && e == hipSuccess; ++i) e = hipStreamWaitEvent(p->qside[i], p->qfork, 0);
-    if (e != hipSuccess) return hip_fail(e, "quotient fork");
-    const void* src[2] = {d_A, d_B};
-    Fe* dst[2] = {t1, t2};
-    int rc = ZK_OK;
-    for (int i = 0; i < 2 && rc == ZK_OK; ++i) {
-      Fe* wi = ws ? w + (size_t)(i + 1) * ws : nullptr;
-      rc = run_transform(p, kInverseRaw, src[i], dst[i], wi, p->qside[i]);
-      if (rc == ZK_OK) rc = run_transform(p, kForwardShifted, dst[i], dst[i], wi, p->qside[i]);
-    }
-    if (rc == ZK_OK) rc = run_transform(p, kInverseRaw, d_C, H, w, s);
-    // join both side streams into s in every case, so that whatever was
-    // queued on them is ordered before later work on s, also after an error
-    for (int i = 0; i < 2; ++i) {
-      e = hipEventRecord(p->qjoin[i], p->qside[i]);
-      if (e == hipSuccess) e = hipStreamWaitEvent(s, p->qjoin[i], 0);
-      if (e != hipSuccess && rc == ZK_OK) rc = hip_fail(e, "quotient join");
-    }
-    if (rc != ZK_OK) return rc;
-    if (int rc = run_forward_pointwise(p, H, H, w, t1, t2, s)) return rc;
+  const size_t P = p->passes.size();
+  if (quotient_groups(p)) {
+    // A's, B's and C's transforms advance together, each pass one launch for
+    // all three, but for C's last pass: it takes A's and B's values in its
+    // pointwise step.
+    Vectors inv[3] = {{d_A, t1, w}, {d_B, t2, w ? w + ws : nullptr}, {d_C, H, w ? w + 2 * ws : nullptr}};
+    Vectors fwd[3];
+    for (int v = 0; v < 3; ++v) fwd[v] = Vectors{inv[v].out, inv[v].out, inv[v].work};
+    if (int rc = run_grouped(p, kInverseRaw, inv, 3, 0, P, s)) return rc;
+    if (int rc = run_grouped(p, kForwardShifted, fwd, 3, 0, P - 1, s)) return rc;
+    if (int rc = run_grouped(p, kForwardShifted, fwd, 2, P - 1, P, s)) return rc;
+    if (int rc = run_last_pointwise(p, H, H, fwd[2].work, t1, t2, s)) return rc;
     return run_transform(p, kCosetInverse, H, H, w, s);
   }
   // Each of A, B, C: INTT without its 1/n, then a forward NTT that multiplies
@@ -781,8 +769,10 @@ int quotient_poly(const ntt_plan* p, const void* d_A, const void* d_B, const voi
     if (int rc = run_transform(p, kInverseRaw, src[v], dst[v], w, s)) return rc;
     if (v < 2) {
       if (int rc = run_transform(p, kForwardShifted, dst[v], dst[v], w, s)) return rc;
-    } else if (int rc = run_forward_pointwise(p, H, H, w, t1, t2, s)) {
-      return rc;
+    } else {
+      const Vectors c{H, H, w};
+      if (int rc = run_grouped(p, kForwardShifted, &c, 1, 0, P - 1, s)) return rc;
+      if (int rc = run_last_pointwise(p, H, H, w, t1, t2, s)) return rc;
     }
   }
   return run_transform(p, kCosetInverse, H, H, w, s);
@@ -1224,7 +1214,8 @@ int batch_build(ntt_batch** out, const ntt_batch_job* specs, int njobs, bool cap
   // (grouped launches), ahead of the persistent kernel in the same stream.
   // Which groups do is chosen greedily on a time estimate, with constants
   // measured on MI355X: the grouped launches take, per pass, a launch gap
-  // plus rounds of pass tiles over the chip; the persistent kernel takes the
+  // plus the larger of a lone pass's latency and the elements at the rate of a
+  // full chip; the persistent kernel takes the
   // larger of its items spread over all its workgroups and its largest job
   // alone on one XCD.  A group moves while that lowers the estimated total.
   // A pointwise job runs on its own when it is more than an eighth of the
@@ -1260,18 +1251,16 @@ int batch_build(ntt_batch** out, const ntt_batch_job* specs, int njobs, bool cap
   for (int k = 0; k < njobs; ++k)
     if (jobs[k].kind == zk::kJobPointwise) direct[k] = all_direct || load(k) * zk::kXcds > total;
   constexpr double kLaunchUs = 4.0;      // gap between dependent launches
-  constexpr double kRoundUs = 40.0;      // one round of 2^10-element pass tiles, 4 per CU
+  constexpr double kPassUs = 6.0;        // shortest pass
+  constexpr double kUsPerElem = 33.0 / (1 << 20);  // a pass that fills the chip, per element
   constexpr double kBatchItemUs = 70.0;  // one 2^11-element item of the persistent kernel
   const double batch_slots = (double)cus * zk::batch_workgroups_per_cu();
   const size_t G = groups.size();
   std::vector<double> grouped_us(G), group_items(G), alone_us(G);
   for (size_t g = 0; g < G; ++g) {
     const ntt_plan* p = specs[groups[g][0]].plan;
-    const int log_tile = p->passes[0].log_tile;
-    const uint64_t tiles = (p->n >> log_tile) * groups[g].size();  // per pass, at the plan's tile
-    const double slots = (double)cus * (log_tile >= 11 ? 2 : 4);
-    const double round_us = kRoundUs * std::ldexp(1.0, log_tile - 10);  // a round's work scales with the tile
-    grouped_us[g] = (double)p->passes.size() * (kLaunchUs + std::ceil((double)tiles / slots) * round_us);
+    grouped_us[g] = (double)p->passes.size() *
+                    (kLaunchUs + std::max(kPassUs, kUsPerElem * (double)p->n * (double)groups[g].size()));
     group_items[g] = (double)(load(groups[g][0]) * groups[g].size());
     alone_us[g] = (double)load(groups[g][0]) * kBatchItemUs / (batch_slots / zk::kXcds);
   }
@@ -1397,8 +1386,9 @@ int batch_build(ntt_batch** out, const ntt_batch_job* specs, int njobs, bool cap
   b->grid = (uint32_t)std::min<size_t>(items.size(), (size_t)cus * (beside ? 1 : zk::batch_workgroups_per_cu()));
   // Direct work goes to up to kSideStreams side streams, dealt largest first
   // (by tiles over all passes) to the least loaded, so that groups too small
-  // to fill the chip alone run at the same time.
-  constexpr size_t kSideStreams = 3;
+  // to fill the chip alone run at the same time (64-job batch: 0.411 ms with
+  // three, 0.390 with four, 0.397 with six).
+  constexpr size_t kSideStreams = 4;
   const size_t nsides = std::min(kSideStreams, b->direct.size());
   if (nsides > 1 || beside) {
     std::vector<size_t> order(b->direct.size());
@@ -1427,11 +1417,8 @@ int batch_build(ntt_batch** out, const ntt_batch_job* specs, int njobs, bool cap
       std::vector<double> lane_us(nsides, 0.0);
       for (const DirectWork& d : b->direct) {
         if (d.pointwise) continue;
-        const int log_tile = d.plan->passes[0].log_tile;
-        const double tiles = (double)(d.plan->n >> log_tile) * std::max<uint32_t>(1, d.pass[0].grp_jobs);
-        const double slots = (double)cus * (log_tile >= 11 ? 2 : 4);
-        lane_us[d.lane] += (double)d.pass.size() *
-                           (kLaunchUs + std::ceil(tiles / slots) * kRoundUs * std::ldexp(1.0, log_tile - 10));
+        const double elems = (double)d.plan->n * std::max<uint32_t>(1, d.pass[0].grp_jobs);
+        lane_us[d.lane] += (double)d.pass.size() * (kLaunchUs + std::max(kPassUs, kUsPerElem * elems));
       }
       const double longest = *std::max_element(lane_us.begin(), lane_us.end());
       const uint32_t half = (uint32_t)std::max(1, cus / 2);

@@ -45,12 +45,32 @@ struct PassArgs {
   // Grouped launch (grp_jobs > 0): one launch runs this pass for grp_jobs
   // transforms of one plan, 2^log_grp_tiles tiles each; workgroup b takes
   // tile b mod 2^log_grp_tiles of job b / 2^log_grp_tiles, reading
-  // grp_in[job] and writing grp_out[job] in place of in and out.
+  // grp_in[job] and writing grp_out[job] in place of in and out.  With grp_in
+  // null, up to kMaxFew jobs have their pointers here: job 0 in and out, the
+  // others few_in and few_out.
   const Fe* const* grp_in;
   Fe* const* grp_out;
   uint32_t grp_jobs;
   uint32_t log_grp_tiles;
+  const Fe* few_in[2];
+  Fe* few_out[2];
 };
+constexpr uint32_t kMaxFew = 3;
+
+// The tile of workgroup `block`; in a grouped launch its job's vectors become
+// a.in and a.out.
+__device__ __forceinline__ uint32_t pass_tile_index(PassArgs& a, uint32_t block) {
+  if (!a.grp_jobs) return block;
+  const uint32_t job = block >> a.log_grp_tiles;
+  if (a.grp_in) {
+    a.in = a.grp_in[job];
+    a.out = a.grp_out[job];
+  } else if (job) {
+    a.in = job == 1 ? a.few_in[0] : a.few_in[1];
+    a.out = job == 1 ? a.few_out[0] : a.few_out[1];
+  }
+  return block & ((1u << a.log_grp_tiles) - 1u);
+}
 
 // Transforms of at most 2^kTinyLog points run in one workgroup of the
 // register kernels (ntt_pass_impl.hpp).

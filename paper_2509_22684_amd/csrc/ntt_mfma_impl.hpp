@@ -396,13 +396,7 @@ __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS)
   using Rd = typename S::Rd;
   __shared__ U32x4 lds[S::LDS_DATA + S::LDS_A];
   constexpr int K = group<S::U>();
-  uint32_t tile = blockIdx.x;
-  if (a.grp_jobs) {
-    const uint32_t job = blockIdx.x >> a.log_grp_tiles;
-    tile = blockIdx.x & ((1u << a.log_grp_tiles) - 1u);
-    a.in = a.grp_in[job];
-    a.out = a.grp_out[job];
-  }
+  const uint32_t tile = pass_tile_index(a, blockIdx.x);
   const U32x4* frag = reinterpret_cast<const U32x4*>(&digit_table<F>);
   for (uint32_t k = threadIdx.x; k < 16 * 64; k += S::THREADS) lds[S::LDS_DATA + k] = frag[k];
 
@@ -522,14 +516,21 @@ hipError_t launch_one(const PassArgs& a0, hipStream_t s) {
 }
 
 // Elements per lane by the number of elements in the launch (all jobs of a
-// grouped one): one while the launch does not fill the chip (each of a lane's
-// elements adds to the pass's latency: radix 2^8 at 2^16, 7.0 / 8.3 us for
-// the first / last pass with one, 7.4 / 9.2 with two), two up to 2^20 (radix
-// 2^7 at 2^19: 16.0 / 21.6 us with two, 18.9 / 23.5 with one, 17.2 / 24.3 with
-// four), then four in 2^10-element tiles, which read and write twice as long
-// runs (radix 2^8 at 2^24: 0.464 / 0.615 ms with four, 0.493 / 0.751 with two
-// in 2^9-element tiles, 0.518 / 0.679 in 2^10).
+// grouped one).  One while the launch does not fill the chip: each of a lane's
+// elements adds to the pass's latency (radix 2^8 at 2^16, 7.0 / 8.3 us for the
+// first / last pass with one, 7.4 / 9.2 with two).  Then two or four, whichever
+// needs the shorter rounds of resident workgroups: 256 CUs hold about 1,280
+// workgroups of 2^9 elements or 768 of 2^10, and a round of the latter takes
+// about 1.13 times as long (radix 2^7 at 2^20: 1.6 rounds against 1.3, 27.7 /
+// 36.3 us against 32.8 / 40.8; at 2^19 16.0 / 21.6 against 17.2 / 24.3).  From
+// 2^21 always four: their tiles read and write runs twice as long (radix 2^8
+// at 2^24: 0.442 / 0.589 ms against 0.493 / 0.751).
 constexpr uint32_t kTwoLog = 18, kFourLog = 21;
+inline bool four_per_lane(uint64_t elements) {
+  if (elements >> kFourLog) return true;
+  const uint64_t rounds4 = ((elements >> 10) + 767) / 768, rounds2 = ((elements >> 9) + 1279) / 1280;
+  return 113 * rounds4 < 100 * rounds2;
+}
 
 // Passes of multi-pass transforms (radix 2^3 .. 2^9), and transforms of 2^8
 // to 2^11 points in one tile.  Keep in step with mfma_supported().
@@ -545,7 +546,7 @@ hipError_t dispatch(int log_r, const PassArgs& a, hipStream_t s) {
     }
   }
   const uint64_t total = (a.grp_jobs ? a.grp_jobs : 1ull) << a.log_n;
-  if (total >> kFourLog && a.log_n >= 10) {
+  if (total >> kTwoLog && a.log_n >= 10 && four_per_lane(total)) {
     switch (log_r) {
       case 3: return launch_one<F, 3, 10, 8>(a, s);
       case 4: return launch_one<F, 4, 10, 8>(a, s);

@@ -413,13 +413,7 @@ __global__ void __launch_bounds__((PassShape<LOG_R, LOG_TILE, LOG_E>::THREADS),
     ntt_pass_kernel(PassArgs a) {
   using S = PassShape<LOG_R, LOG_TILE, LOG_E>;
   __shared__ Fe lds[S::LDS_SLOTS];
-  uint32_t tile = blockIdx.x;
-  if (a.grp_jobs) {
-    const uint32_t job = blockIdx.x >> a.log_grp_tiles;
-    tile = blockIdx.x & ((1u << a.log_grp_tiles) - 1u);
-    a.in = a.grp_in[job];
-    a.out = a.grp_out[job];
-  }
+  const uint32_t tile = pass_tile_index(a, blockIdx.x);
   pass_tile<F, LOG_R, LOG_TILE, LOG_E>(a, tile, lds, threadIdx.x, true);
 }
 
