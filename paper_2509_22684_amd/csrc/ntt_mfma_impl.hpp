@@ -397,8 +397,13 @@ __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS)
   __shared__ U32x4 lds[S::LDS_DATA + S::LDS_A];
   constexpr int K = group<S::U>();
   const uint32_t tile = pass_tile_index(a, blockIdx.x);
-  const U32x4* frag = reinterpret_cast<const U32x4*>(&digit_table<F>);
-  for (uint32_t k = threadIdx.x; k < 16 * 64; k += S::THREADS) lds[S::LDS_DATA + k] = frag[k];
+  // the matrices are fetched beside the first data and reach LDS after them
+  constexpr int FRAGS = 16 * 64 / S::THREADS;
+  U32x4 frag[FRAGS];
+  sfor<FRAGS>([&](auto k_) {
+    constexpr int k = decltype(k_)::value;
+    frag[k] = reinterpret_cast<const U32x4*>(&digit_table<F>)[k * S::THREADS + threadIdx.x];
+  });
 
   const uint64_t n = 1ull << a.log_n, ns = 1ull << a.log_ns;
   const uint64_t j0 = (uint64_t)tile << S::LOG_J;
@@ -455,6 +460,10 @@ __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS)
     }
     store_digits<F, S::HALF, K>(lds, slot, x, reduce);
   }
+  sfor<FRAGS>([&](auto k_) {
+    constexpr int k = decltype(k_)::value;
+    lds[S::LDS_DATA + k * S::THREADS + threadIdx.x] = frag[k];
+  });
   __syncthreads();
 
   rounds<F, LOG_R, LOG_TILE, LOG_THREADS, 0>(lds, a.tw_r);
