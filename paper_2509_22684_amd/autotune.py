@@ -6,10 +6,11 @@ at run time (Section V-A).  For every (field, log2 n) this module times the
 candidate schedules of the C library on the current device — how many
 butterfly stages one global pass fuses (log2_pass_radix), where inter-pass
 twiddles come from (a precomputed table per pass, or two small tables and one
-extra multiplication), the tile a workgroup holds (2^11 or 2^10 elements:
-fewer, larger workgroups or more, smaller ones per CU) and the in-register
-radix — and records the fastest
-in a JSON database keyed by device name.  Every candidate computes the same
+extra multiplication), the tile a workgroup holds and the in-register radix
+(the last two choose kernels of the FP64 product only, and whether up to 2^11
+points run as one tile; the matrix-core passes choose their tiles by the
+launch's size) — and records the fastest in a JSON database keyed by device
+name.  Every candidate computes the same
 bytes (the GPU tests check each schedule against the oracle), so tuning only
 changes speed.
 
@@ -40,7 +41,7 @@ def candidates(log2n: int, batchable: bool = False) -> list[dict]:
         return [dict(log2_radix=2, log2_pass_radix=pr, twiddle_mode=tm) for pr in (6, 7, 8, 9) for tm in (1, 2)]
     out = [dict(log2_radix=2, log2_pass_radix=pr, twiddle_mode=tm, log2_tile=tile)
            for pr in (6, 7, 8, 9) for tm in (1, 2) for tile in (11, 10)]
-    # radix-2 and radix-8 register rounds on the default split
+    # the other register radices on the default split
     out += [dict(log2_radix=1), dict(log2_radix=3)]
     if log2n <= 16:  # small transforms: 2^8-element tiles spread a pass over more CUs
         out += [dict(log2_radix=e, log2_tile=8) for e in (1, 2)]

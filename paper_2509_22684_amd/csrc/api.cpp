@@ -170,15 +170,18 @@ void free_plan(ntt_plan* p) {
 // Up to 2^22 one transform does not fill the chip, or leaves a large part of
 // its last round of workgroups empty, and the quotient chain advances A, B and
 // C together, each pass one launch for all three, with a transform workspace
-// each.  Against A's and B's chains on two side streams beside C's: 2^14 55
-// and 112 us, 2^18 220 and 290, 2^19 407 and 377 to 420, 2^21 1470 and 1545,
-// 2^22 2.92 and 2.89 ms (there the streams' overlap depends on the hardware
-// queues they fall on).
+// each.  Against A's and B's chains on two side streams beside C's, before the
+// transforms were bridged: 2^14 55 and 112 us, 2^18 220 and 290, 2^19 407 and
+// 377 to 420, 2^21 1470 and 1545, 2^22 2.92 and 2.89 ms (there the streams'
+// overlap depends on the hardware queues they fall on).
 constexpr uint32_t kQuotientGroupMaxLog = 22;
 bool quotient_groups(const ntt_plan* p) { return p->log_n <= kQuotientGroupMaxLog; }
 
-// Split log_n into passes of at most max_log_r stages each, larger radices
-// first (a single pass covers n up to the tile size in one tile).  A column
+// Split log_n into passes of at most max_log_r stages each (a single pass
+// covers n up to the tile size in one tile).  Three passes have equal radices
+// at the ends, so that the quotient chain can bridge its transforms; otherwise
+// larger radices come first.  (A plain transform takes the same time either
+// way: 2^20 94 us, 2^22 361 and 364 us.)  A column
 // of the FP64 kernels' tiles holds fewer points than the tile; the
 // matrix-core kernels choose their tiles to fit the radix.
 std::vector<int> split_passes(uint32_t log_n, const ntt_plan_opts& o) {
@@ -192,6 +195,7 @@ std::vector<int> split_passes(uint32_t log_n, const ntt_plan_opts& o) {
   const int P = (int)((log_n + max_log_r - 1) / max_log_r);
   const int base = (int)log_n / P, extra = (int)log_n % P;
   for (int k = 0; k < P; ++k) r.push_back(base + (k < extra ? 1 : 0));
+  if (P == 3 && extra) r[0] = r[2] = base + (extra == 2), r[1] = base + (extra == 1);
   return r;
 }
 
@@ -418,12 +422,16 @@ int validate_input(ntt_plan* p, const void* x, hipStream_t s) {
 // workspace and `out` (pass k writes work when k is even).  With an odd
 // number of passes the last one reads and writes `out` in place, which is
 // safe because the last pass writes exactly the elements each tile reads.
-zk::PassArgs make_pass_args(const ntt_plan* p, Kind kind, size_t k, const void* in, void* out, void* work) {
+// `swapped`: pass 0 wrote `out`, and the passes after it alternate the other
+// way.
+zk::PassArgs make_pass_args(const ntt_plan* p, Kind kind, size_t k, const void* in, void* out, void* work,
+                            bool swapped = false) {
   const size_t P = p->passes.size();
   const PassDesc& d = p->passes[k];
   zk::PassArgs a{};
-  a.in = static_cast<const Fe*>(k == 0 ? in : (k % 2 == 1 ? work : out));
-  a.out = static_cast<Fe*>(k + 1 == P ? out : (k % 2 == 0 ? work : out));
+  const size_t turn = swapped ? k + 1 : k;
+  a.in = static_cast<const Fe*>(k == 0 ? in : (turn % 2 == 1 ? work : out));
+  a.out = static_cast<Fe*>(k + 1 == P ? out : (turn % 2 == 0 ? work : out));
   a.tw_pass = d.tw_pass;
   a.tw_r = d.tw_r;
   if (k > 0 && !d.tw_pass) {
@@ -483,19 +491,23 @@ int run_transform(const ntt_plan* p, Kind kind, const void* in, void* out, void*
 }
 
 // Passes first .. end - 1 of `jobs` (at most kMaxFew) transforms of one kind, a
-// launch per pass for all of them.
+// launch per pass for all of them.  adjust(args, k): further arguments of pass k.
 struct Vectors {
   const void* in;
   void* out;
   void* work;
 };
-int run_grouped(const ntt_plan* p, Kind kind, const Vectors* v, uint32_t jobs, size_t first, size_t end, hipStream_t s) {
+template <class Adjust>
+int run_grouped(const ntt_plan* p, Kind kind, const Vectors* v, uint32_t jobs, size_t first, size_t end, hipStream_t s,
+                bool swapped, Adjust adjust) {
   for (size_t k = first; k < end; ++k) {
     const PassDesc& d = p->passes[k];
-    zk::PassArgs a = make_pass_args(p, kind, k, v[0].in, v[0].out, v[0].work);
+    zk::PassArgs a = make_pass_args(p, kind, k, v[0].in, v[0].out, v[0].work, swapped);
     a.grp_jobs = jobs;
+    adjust(a, v[0]);
     for (uint32_t j = 1; j < jobs; ++j) {
-      const zk::PassArgs b = make_pass_args(p, kind, k, v[j].in, v[j].out, v[j].work);
+      zk::PassArgs b = make_pass_args(p, kind, k, v[j].in, v[j].out, v[j].work, swapped);
+      adjust(b, v[j]);
       a.few_in[j - 1] = b.in;
       a.few_out[j - 1] = b.out;
     }
@@ -504,23 +516,70 @@ int run_grouped(const ntt_plan* p, Kind kind, const Vectors* v, uint32_t jobs, s
   }
   return ZK_OK;
 }
+int run_grouped(const ntt_plan* p, Kind kind, const Vectors* v, uint32_t jobs, size_t first, size_t end, hipStream_t s,
+                bool swapped = false) {
+  return run_grouped(p, kind, v, jobs, first, end, s, swapped, [](zk::PassArgs&, const Vectors&) {});
+}
 
 size_t workspace_elems(const ntt_plan* p) { return p->passes.size() >= 2 ? p->n : 0; }
 
-// The last pass of a forward NTT of `in` that also applies the quotient's
-// pointwise step with the coset evaluations a and b:
-// out = (a b - NTT(in)) / (g^n - 1).
-int run_last_pointwise(const ntt_plan* p, const void* in, void* out, void* work, const Fe* a, const Fe* b,
-                       hipStream_t s) {
-  const size_t k = p->passes.size() - 1;
-  const PassDesc& d = p->passes[k];
-  zk::PassArgs args = make_pass_args(p, kForwardShifted, k, in, out, work);
-  args.flags |= zk::kPassPostPointwise;
-  args.pw_a = a;
-  args.pw_b = b;
-  args.post_const = p->zinv;
-  hipError_t e = zk::launch_pass(p->field, d.log_r, d.log_tile, args, s);
-  return e == hipSuccess ? ZK_OK : hip_fail(e, "NTT pass launch");
+// The quotient chain's transforms follow one another directly; where a plan's
+// first and last radix agree, both passes work on the same columns and are one
+// launch (four passes over memory less per chain; two-pass plans of odd log_n
+// keep them apart).  Measured with and without: 2^14 50 and 55 us, 2^20 648
+// and 680 us, 2^24 11.6 and 12.0 ms; faster at every size tried.
+bool bridges(const ntt_plan* p) {
+  const size_t P = p->passes.size();
+  return P >= 2 && !p->fp64 && p->passes[0].log_r == p->passes[P - 1].log_r && zk::bridge_supported(p->passes[0].log_r);
+}
+
+// Evaluations on g<w> of `jobs` vectors given on <w>, up to the last pass: the
+// INTT without its 1/n, then a forward NTT that multiplies coefficient k by
+// g^k / n as its first pass loads it.  (Scaling in the forward's first pass
+// rather than the inverse's last pass puts the product where the pass has no
+// inter-pass twiddle.)  v[j].in is the input, the passes use v[j].out and
+// v[j].work.  *swapped: see make_pass_args.
+int run_to_coset(const ntt_plan* p, const Vectors* v, uint32_t jobs, hipStream_t s, bool* swapped) {
+  const size_t P = p->passes.size();
+  *swapped = false;
+  if (!bridges(p)) {
+    if (int rc = run_grouped(p, kInverseRaw, v, jobs, 0, P, s)) return rc;
+    Vectors fwd[zk::kMaxFew];
+    for (uint32_t j = 0; j < jobs; ++j) fwd[j] = Vectors{v[j].out, v[j].out, v[j].work};
+    return run_grouped(p, kForwardShifted, fwd, jobs, 0, P - 1, s);
+  }
+  if (int rc = run_grouped(p, kInverseRaw, v, jobs, 0, P - 1, s)) return rc;
+  // the bridge writes whichever of out and work it doesn't read
+  *swapped = P % 2 == 0;
+  auto bridge = [&](zk::PassArgs& a, const Vectors& x) {
+    a.flags |= zk::kPassBridge | zk::kPassPreTable;
+    a.pre_table = p->inv_to_coset;
+    a.out = static_cast<Fe*>(*swapped ? x.out : x.work);
+  };
+  if (int rc = run_grouped(p, kInverseRaw, v, jobs, P - 1, P, s, false, bridge)) return rc;
+  return run_grouped(p, kForwardShifted, v, jobs, 1, P - 1, s, *swapped);
+}
+
+// The rest of the chain: the last pass of C's forward NTT also applies the
+// pointwise step with A's and B's evaluations, (a b - c) / (g^n - 1), so H
+// holds the quotient's coset values without a separate pass over memory, and
+// then the coset INTT of H.
+int run_to_quotient(const ntt_plan* p, const Vectors& c, const Fe* a, const Fe* b, hipStream_t s, bool swapped) {
+  const size_t P = p->passes.size();
+  const Vectors h{c.out, c.out, c.work};
+  const bool bridge = bridges(p);
+  auto pointwise = [&](zk::PassArgs& x, const Vectors& v) {
+    x.flags |= zk::kPassPostPointwise;
+    x.pw_a = a;
+    x.pw_b = b;
+    x.post_const = p->zinv;
+    if (bridge) {  // reads v.out
+      x.flags |= zk::kPassBridge | zk::kPassReverseIn;
+      x.out = static_cast<Fe*>(v.work);
+    }
+  };
+  if (int rc = run_grouped(p, kForwardShifted, &h, 1, P - 1, P, s, swapped, pointwise)) return rc;
+  return run_grouped(p, kCosetInverse, &h, 1, bridge ? 1 : 0, P, s);
 }
 
 int transform_entry(const ntt_plan* p, Kind kind, const void* in, void* out, void* work, void* stream) {
@@ -743,39 +802,26 @@ int quotient_poly(const ntt_plan* p, const void* d_A, const void* d_B, const voi
   Fe* w = ws ? t2 + p->n : nullptr;
   Fe* H = static_cast<Fe*>(d_H);
   const size_t P = p->passes.size();
-  if (quotient_groups(p)) {
+  bool swapped = false;
+  const bool grouped = quotient_groups(p);
+  const Vectors e[2] = {{t1, t1, w}, {t2, t2, w && grouped ? w + ws : w}};  // A's and B's evaluations
+  if (grouped) {
     // A's, B's and C's transforms advance together, each pass one launch for
     // all three, but for C's last pass: it takes A's and B's values in its
     // pointwise step.
-    Vectors inv[3] = {{d_A, t1, w}, {d_B, t2, w ? w + ws : nullptr}, {d_C, H, w ? w + 2 * ws : nullptr}};
-    Vectors fwd[3];
-    for (int v = 0; v < 3; ++v) fwd[v] = Vectors{inv[v].out, inv[v].out, inv[v].work};
-    if (int rc = run_grouped(p, kInverseRaw, inv, 3, 0, P, s)) return rc;
-    if (int rc = run_grouped(p, kForwardShifted, fwd, 3, 0, P - 1, s)) return rc;
-    if (int rc = run_grouped(p, kForwardShifted, fwd, 2, P - 1, P, s)) return rc;
-    if (int rc = run_last_pointwise(p, H, H, fwd[2].work, t1, t2, s)) return rc;
-    return run_transform(p, kCosetInverse, H, H, w, s);
+    const Vectors v[3] = {{d_A, t1, w}, {d_B, t2, w ? w + ws : nullptr}, {d_C, H, w ? w + 2 * ws : nullptr}};
+    if (int rc = run_to_coset(p, v, 3, s, &swapped)) return rc;
+    if (int rc = run_grouped(p, kForwardShifted, e, 2, P - 1, P, s, swapped)) return rc;
+    return run_to_quotient(p, v[2], t1, t2, s, swapped);
   }
-  // Each of A, B, C: INTT without its 1/n, then a forward NTT that multiplies
-  // coefficient k by g^k / n as its first pass loads it: evaluations on
-  // g<w>.  (Scaling in the forward's first pass rather than the inverse's
-  // last pass puts the product where the pass has no inter-pass twiddle.)
-  // The last pass of C's forward NTT also applies the pointwise step
-  // (A B - C) / (g^n - 1), so H holds the quotient's coset values without a
-  // separate pass over memory.
-  const void* src[3] = {d_A, d_B, d_C};
-  Fe* dst[3] = {t1, t2, H};
-  for (int v = 0; v < 3; ++v) {
-    if (int rc = run_transform(p, kInverseRaw, src[v], dst[v], w, s)) return rc;
-    if (v < 2) {
-      if (int rc = run_transform(p, kForwardShifted, dst[v], dst[v], w, s)) return rc;
-    } else {
-      const Vectors c{H, H, w};
-      if (int rc = run_grouped(p, kForwardShifted, &c, 1, 0, P - 1, s)) return rc;
-      if (int rc = run_last_pointwise(p, H, H, w, t1, t2, s)) return rc;
+  const Vectors v[3] = {{d_A, t1, w}, {d_B, t2, w}, {d_C, H, w}};
+  for (int j = 0; j < 3; ++j) {
+    if (int rc = run_to_coset(p, &v[j], 1, s, &swapped)) return rc;
+    if (j < 2) {
+      if (int rc = run_grouped(p, kForwardShifted, &e[j], 1, P - 1, P, s, swapped)) return rc;
     }
   }
-  return run_transform(p, kCosetInverse, H, H, w, s);
+  return run_to_quotient(p, v[2], t1, t2, s, swapped);
 }
 
 int quotient_coset_evals(const ntt_plan* p, const void* d_in, void* d_out, void* d_work, void* stream) {

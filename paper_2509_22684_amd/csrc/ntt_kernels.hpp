@@ -14,7 +14,16 @@ enum PassFlags : uint32_t {
   kPassPostTable = 4u,   // last pass: multiply output k by post_table[k]
   kPassPostConst = 8u,   // last pass: multiply every output by post_const
   kPassPostPointwise = 16u,  // last pass: out_k = (pw_a[k] pw_b[k] - out_k) post_const
+  // The last pass of one transform and the first pass of the next, of the same
+  // plan: output k of column j of the last pass is element j + k n/R, point k
+  // of the first pass's column j (or, read in reverse, of column -j), so a
+  // tile's columns go from one to the other without a trip to memory.
+  // kPassReverseIn and kPassPreTable then belong to the first pass.
+  kPassBridge = 32u,
 };
+
+// Radices the bridge is instantiated for.
+inline bool bridge_supported(int log_r) { return log_r >= 6 && log_r <= 9; }
 
 // Arguments of one global radix-R Stockham pass over n = 2^log_n elements.
 // The pass reads columns j + r (n/R) for r < R, multiplies element r of

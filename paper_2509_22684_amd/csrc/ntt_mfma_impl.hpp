@@ -26,11 +26,24 @@
 namespace zk {
 namespace mfma {
 
+// Compile-time loop, as detail::sfor; the body is inlined at any size.  Left
+// to its estimate, the compiler keeps the larger bodies of kernels that share
+// them as functions, and the arrays they capture go to scratch (336 bytes per
+// lane at radix 2^8; quotient chain 2^24 16.7 ms against 11.8).
+template <class Fn, int... I>
+__device__ __forceinline__ void sfor_impl(Fn& fn, std::integer_sequence<int, I...>) {
+  [[clang::always_inline]] (fn(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class Fn>
+__device__ __forceinline__ void sfor(Fn&& fn) {
+  sfor_impl(fn, std::make_integer_sequence<int, N>{});
+}
+
+
 typedef int V4i __attribute__((ext_vector_type(4)));
 typedef int V16i __attribute__((ext_vector_type(16)));
 using detail::load_fe;
 using detail::mul_many;
-using detail::sfor;
 using detail::store_fe;
 using detail::U32x4;
 
@@ -233,7 +246,7 @@ __device__ __forceinline__ void dft_round(U32x4* lds) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const V4i* amat = reinterpret_cast<const V4i*>(lds + S::LDS_DATA) + lane;
   // element with digit value 0 of this lane's column in column group nt
-  auto base = [&](uint32_t nt) -> uint32_t {
+  auto base = [&](uint32_t nt) __attribute__((always_inline)) -> uint32_t {
     const uint32_t n = nt * 32u + (lane & 31u);
     const uint32_t c = n & (S::J - 1), m = n >> S::LOG_J;
     const uint32_t r = (m & (LOW - 1)) + ((m >> LOG_LOW) << (LOG_LOW + LOG_RHO));
@@ -388,7 +401,12 @@ __device__ __forceinline__ void rounds(U32x4* lds, const Fe* __restrict__ tw_r) 
 template <class F>
 __device__ const DigitTable digit_table = make_digit_table<F>();
 
-template <class F, int LOG_R, int LOG_TILE, int LOG_THREADS>
+// BRIDGE: kPassBridge.  As much arithmetic as the two passes it replaces,
+// without the vector's trip to memory and the launch between them (quotient
+// chain 2^14 55.1 -> 50.0 us, 2^19 356 -> 336, 2^24 12.02 -> 11.62 ms).  Small
+// chains gain by the launch; large ones less than the bytes saved would give,
+// since their passes are held by the power that products and matrices draw.
+template <class F, int LOG_R, int LOG_TILE, int LOG_THREADS, bool BRIDGE>
 __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS),
                                   (Shape<LOG_R, LOG_TILE, LOG_THREADS>::MIN_WAVES))
     mfma_pass_kernel(PassArgs a) {
@@ -409,6 +427,7 @@ __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS)
   const uint64_t j0 = (uint64_t)tile << S::LOG_J;
   const uint32_t log_stride = a.log_n - LOG_R;
   const bool rev = a.flags & kPassReverseIn;
+  const bool rev_load = !BRIDGE && rev;
 
   // load: element e = r J + c is point r of column j0 + c
 #pragma unroll 1
@@ -425,9 +444,9 @@ __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS)
       constexpr int k = decltype(k_)::value;
       const uint32_t e = elem[k];
       const uint64_t idx = j0 + (e & (S::J - 1)) + ((uint64_t)(e >> S::LOG_J) << log_stride);
-      x[k] = load_fe(a.in, rev ? ((n - idx) & (n - 1)) : idx);
+      x[k] = load_fe(a.in, rev_load ? ((n - idx) & (n - 1)) : idx);
     });
-    if (a.flags & kPassPreTable) {
+    if (!BRIDGE && (a.flags & kPassPreTable)) {
       sfor<K>([&](auto k_) {
         constexpr int k = decltype(k_)::value;
         const uint32_t e = elem[k];
@@ -468,10 +487,56 @@ __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS)
 
   rounds<F, LOG_R, LOG_TILE, LOG_THREADS, 0>(lds, a.tw_r);
 
-  // store: output k of column c sits at the slot with the digits of
-  // (i_1, i_2, ...) in place of (r_1, r_2, ...).  The first pass writes J R consecutive
-  // elements, output index fastest; later passes write runs of J columns.
-  const bool k_fast = a.log_ns == 0;
+  // output k of column c sits at the slot with the digits of (i_1, i_2, ...)
+  // in place of (r_1, r_2, ...)
+  auto out_slot = [&](uint32_t k, uint32_t c) __attribute__((always_inline)) -> uint32_t {
+    uint32_t r = 0;
+    sfor<Rd::N>([&](auto d_) {
+      constexpr int d = decltype(d_)::value;
+      r |= out_digit<S::HALF, Rd::log(d)>((k >> Rd::high(d)) & ((1u << Rd::log(d)) - 1)) << Rd::low(d);
+    });
+    return slot16((r << S::LOG_J) + c, 0);
+  };
+  // the quotient's pointwise step: (A B - C) / (g^n - 1), C this output
+  auto pointwise = [&](const Fe& x, uint64_t idx) __attribute__((always_inline)) -> Fe {
+    const Fe ab = mul<F>(load_fe(a.pw_a, idx), load_fe(a.pw_b, idx));
+    return mul<F, false>(sub_lazy<F>(ab, x), a.post_const);
+  };
+
+  if constexpr (BRIDGE) {
+    static_assert(K == S::U, "every output is taken before any is overwritten");
+    Fe x[K], w[K];
+    uint32_t slot[K];
+    uint64_t idx[K];
+    sfor<K>([&](auto k_) {
+      constexpr int k = decltype(k_)::value;
+      const uint32_t e = S::HALF ? elem_at<LOG_TILE - 1, S::THREADS>(k) : threadIdx.x;
+      const uint32_t c = e & (S::J - 1), r = e >> S::LOG_J;
+      // point r of column -j is element n - (j + i n/R): i = R - 1 - r, or -r if j = 0
+      const uint32_t i = rev ? (S::R - (j0 + c ? 1u : 0u) - r) & (S::R - 1) : r;
+      slot[k] = slot16(e, 0);
+      idx[k] = j0 + c + ((uint64_t)i << log_stride);
+      x[k] = lds_load(lds, out_slot(i, c));
+    });
+    if (a.flags & kPassPreTable) {
+      sfor<K>([&](auto k_) { w[decltype(k_)::value] = load_fe(a.pre_table, idx[decltype(k_)::value]); });
+      mul_many<F, K, K>(x, w);
+    }
+    if (a.flags & kPassPostPointwise) {
+      sfor<K>([&](auto k_) {
+        constexpr int k = decltype(k_)::value;
+        x[k] = pointwise(x[k], idx[k]);
+      });
+    }
+    __syncthreads();
+    store_digits<F, S::HALF, K>(lds, slot, x, true);
+    __syncthreads();
+    rounds<F, LOG_R, LOG_TILE, LOG_THREADS, 0>(lds, a.tw_r);
+  }
+
+  // store: the first pass writes J R consecutive elements, output index
+  // fastest; later passes write runs of J columns.
+  const bool k_fast = BRIDGE || a.log_ns == 0;
 #pragma unroll 1
   for (int it = 0; it < S::U; it += K) {
     Fe x[K], w[K];
@@ -481,46 +546,44 @@ __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS)
       const uint32_t e = (it + q) * S::THREADS + threadIdx.x;
       const uint32_t c = k_fast ? e >> LOG_R : e & (S::J - 1);
       const uint32_t k = k_fast ? e & (S::R - 1) : e >> S::LOG_J;
-      uint32_t r = 0;
-      sfor<Rd::N>([&](auto d_) {
-        constexpr int d = decltype(d_)::value;
-        r |= out_digit<S::HALF, Rd::log(d)>((k >> Rd::high(d)) & ((1u << Rd::log(d)) - 1)) << Rd::low(d);
-      });
-      x[q] = lds_load(lds, slot16((r << S::LOG_J) + c, 0));
+      x[q] = lds_load(lds, out_slot(k, c));
       const uint64_t j = j0 + c;
-      idx[q] = ((j >> a.log_ns) << (a.log_ns + LOG_R)) + (j & (ns - 1)) + ((uint64_t)k << a.log_ns);
+      if constexpr (BRIDGE)
+        idx[q] = ((rev ? ((1ull << log_stride) - j) & ((1ull << log_stride) - 1) : j) << LOG_R) + k;
+      else
+        idx[q] = ((j >> a.log_ns) << (a.log_ns + LOG_R)) + (j & (ns - 1)) + ((uint64_t)k << a.log_ns);
     });
-    if (a.flags & kPassPostTable) {
-      sfor<K>([&](auto q_) { w[decltype(q_)::value] = load_fe(a.post_table, idx[decltype(q_)::value]); });
-      mul_many<F, K, K>(x, w);
-    }
-    if (a.flags & kPassPostConst) {
-      sfor<K>([&](auto q_) { w[decltype(q_)::value] = a.post_const; });
-      mul_many<F, K, K>(x, w);
-    }
-    if (a.flags & kPassPostPointwise) {
-      // the quotient's pointwise step: (A B - C) / (g^n - 1), C this output
-      sfor<K>([&](auto q_) {
-        constexpr int q = decltype(q_)::value;
-        const Fe ab = mul<F>(load_fe(a.pw_a, idx[q]), load_fe(a.pw_b, idx[q]));
-        x[q] = mul<F, false>(sub_lazy<F>(ab, x[q]), a.post_const);
-      });
-    }
-    if (a.log_ns + LOG_R == a.log_n) {  // the last pass's outputs are canonical
-      sfor<K>([&](auto q_) { x[decltype(q_)::value] = canon<F>(x[decltype(q_)::value]); });
+    if constexpr (!BRIDGE) {
+      if (a.flags & kPassPostTable) {
+        sfor<K>([&](auto q_) { w[decltype(q_)::value] = load_fe(a.post_table, idx[decltype(q_)::value]); });
+        mul_many<F, K, K>(x, w);
+      }
+      if (a.flags & kPassPostConst) {
+        sfor<K>([&](auto q_) { w[decltype(q_)::value] = a.post_const; });
+        mul_many<F, K, K>(x, w);
+      }
+      if (a.flags & kPassPostPointwise) {
+        sfor<K>([&](auto q_) {
+          constexpr int q = decltype(q_)::value;
+          x[q] = pointwise(x[q], idx[q]);
+        });
+      }
+      if (a.log_ns + LOG_R == a.log_n) {  // the last pass's outputs are canonical
+        sfor<K>([&](auto q_) { x[decltype(q_)::value] = canon<F>(x[decltype(q_)::value]); });
+      }
     }
     sfor<K>([&](auto q_) { store_fe(a.out, idx[decltype(q_)::value], x[decltype(q_)::value]); });
   }
 }
 
-template <class F, int LOG_R, int LOG_TILE, int LOG_THREADS>
+template <class F, bool BRIDGE, int LOG_R, int LOG_TILE, int LOG_THREADS>
 hipError_t launch_one(const PassArgs& a0, hipStream_t s) {
   using S = Shape<LOG_R, LOG_TILE, LOG_THREADS>;
   PassArgs a = a0;
   a.log_grp_tiles = a.log_n - LOG_TILE;
   const uint64_t tiles = ((1ull << a.log_n) >> LOG_TILE) * (a.grp_jobs ? a.grp_jobs : 1u);
-  hipLaunchKernelGGL((mfma_pass_kernel<F, LOG_R, LOG_TILE, LOG_THREADS>), dim3((uint32_t)tiles), dim3(S::THREADS), 0, s,
-                     a);
+  hipLaunchKernelGGL((mfma_pass_kernel<F, LOG_R, LOG_TILE, LOG_THREADS, BRIDGE>), dim3((uint32_t)tiles),
+                     dim3(S::THREADS), 0, s, a);
   return hipGetLastError();
 }
 
@@ -541,54 +604,72 @@ inline bool four_per_lane(uint64_t elements) {
   return 113 * rounds4 < 100 * rounds2;
 }
 
-// Passes of multi-pass transforms (radix 2^3 .. 2^9), and transforms of 2^8
-// to 2^11 points in one tile.  Keep in step with mfma_supported().
-template <class F>
-hipError_t dispatch(int log_r, const PassArgs& a, hipStream_t s) {
-  if ((uint32_t)log_r == a.log_n) {
-    switch (log_r) {
-      case 8: return launch_one<F, 8, 8, 8>(a, s);
-      case 9: return launch_one<F, 9, 9, 9>(a, s);
-      case 10: return launch_one<F, 10, 10, 10>(a, s);
-      case 11: return launch_one<F, 11, 11, 10>(a, s);
-      default: return hipErrorInvalidValue;
-    }
-  }
+// Passes of multi-pass transforms (radix 2^3 .. 2^9; bridges 2^6 .. 2^9).
+template <class F, bool BRIDGE>
+hipError_t dispatch_multi(int log_r, const PassArgs& a, hipStream_t s) {
   const uint64_t total = (a.grp_jobs ? a.grp_jobs : 1ull) << a.log_n;
   if (total >> kTwoLog && a.log_n >= 10 && four_per_lane(total)) {
+    if constexpr (!BRIDGE) {
+      switch (log_r) {
+        case 3: return launch_one<F, BRIDGE, 3, 10, 8>(a, s);
+        case 4: return launch_one<F, BRIDGE, 4, 10, 8>(a, s);
+        case 5: return launch_one<F, BRIDGE, 5, 10, 8>(a, s);
+      }
+    }
     switch (log_r) {
-      case 3: return launch_one<F, 3, 10, 8>(a, s);
-      case 4: return launch_one<F, 4, 10, 8>(a, s);
-      case 5: return launch_one<F, 5, 10, 8>(a, s);
-      case 6: return launch_one<F, 6, 10, 8>(a, s);
-      case 7: return launch_one<F, 7, 10, 8>(a, s);
-      case 8: return launch_one<F, 8, 10, 8>(a, s);
-      case 9: return launch_one<F, 9, 10, 8>(a, s);
+      case 6: return launch_one<F, BRIDGE, 6, 10, 8>(a, s);
+      case 7: return launch_one<F, BRIDGE, 7, 10, 8>(a, s);
+      case 8: return launch_one<F, BRIDGE, 8, 10, 8>(a, s);
+      case 9: return launch_one<F, BRIDGE, 9, 10, 8>(a, s);
       default: return hipErrorInvalidValue;
     }
   }
   if (total >> kTwoLog && a.log_n >= 9) {
+    if constexpr (!BRIDGE) {
+      switch (log_r) {
+        case 3: return launch_one<F, BRIDGE, 3, 9, 8>(a, s);
+        case 4: return launch_one<F, BRIDGE, 4, 9, 8>(a, s);
+        case 5: return launch_one<F, BRIDGE, 5, 9, 8>(a, s);
+      }
+    }
     switch (log_r) {
-      case 3: return launch_one<F, 3, 9, 8>(a, s);
-      case 4: return launch_one<F, 4, 9, 8>(a, s);
-      case 5: return launch_one<F, 5, 9, 8>(a, s);
-      case 6: return launch_one<F, 6, 9, 8>(a, s);
-      case 7: return launch_one<F, 7, 9, 8>(a, s);
-      case 8: return launch_one<F, 8, 9, 8>(a, s);
-      case 9: return launch_one<F, 9, 10, 9>(a, s);
+      case 6: return launch_one<F, BRIDGE, 6, 9, 8>(a, s);
+      case 7: return launch_one<F, BRIDGE, 7, 9, 8>(a, s);
+      case 8: return launch_one<F, BRIDGE, 8, 9, 8>(a, s);
+      case 9: return launch_one<F, BRIDGE, 9, 10, 9>(a, s);
       default: return hipErrorInvalidValue;
     }
   }
+  if constexpr (!BRIDGE) {
+    switch (log_r) {
+      case 3: return launch_one<F, BRIDGE, 3, 8, 8>(a, s);
+      case 4: return launch_one<F, BRIDGE, 4, 9, 9>(a, s);
+      case 5: return launch_one<F, BRIDGE, 5, 8, 8>(a, s);
+    }
+  }
   switch (log_r) {
-    case 3: return launch_one<F, 3, 8, 8>(a, s);
-    case 4: return launch_one<F, 4, 9, 9>(a, s);
-    case 5: return launch_one<F, 5, 8, 8>(a, s);
-    case 6: return launch_one<F, 6, 8, 8>(a, s);
-    case 7: return launch_one<F, 7, 9, 9>(a, s);
-    case 8: return launch_one<F, 8, 9, 9>(a, s);
-    case 9: return launch_one<F, 9, 10, 10>(a, s);
+    case 6: return launch_one<F, BRIDGE, 6, 8, 8>(a, s);
+    case 7: return launch_one<F, BRIDGE, 7, 9, 9>(a, s);
+    case 8: return launch_one<F, BRIDGE, 8, 9, 9>(a, s);
+    case 9: return launch_one<F, BRIDGE, 9, 10, 10>(a, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+// A pass of a multi-pass transform, or a transform of 2^8 to 2^11 points in
+// one tile.  Keep in step with mfma_supported() and bridge_supported().
+template <class F>
+hipError_t dispatch(int log_r, const PassArgs& a, hipStream_t s) {
+  if ((uint32_t)log_r == a.log_n) {
+    switch (log_r) {
+      case 8: return launch_one<F, false, 8, 8, 8>(a, s);
+      case 9: return launch_one<F, false, 9, 9, 9>(a, s);
+      case 10: return launch_one<F, false, 10, 10, 10>(a, s);
+      case 11: return launch_one<F, false, 11, 11, 10>(a, s);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  return a.flags & kPassBridge ? dispatch_multi<F, true>(log_r, a, s) : dispatch_multi<F, false>(log_r, a, s);
 }
 
 }  // namespace mfma

@@ -23,9 +23,9 @@ the batch's persistent kernel, whose workgroups are large, would wait for
 room on CUs that the other lane's pass kernels keep filling.
 
 A lone job runs whole.  When a lane holds a single job that has not
-started, its tick is that job's whole chain as one quotient_poly call (A's
-and B's chains on forked streams, the pointwise step fused): at light load
-a job then costs its stand-alone time instead of four batch builds and four
+started, its tick is that job's whole chain as one quotient_poly call (A,
+B and C advance in shared launches, the pointwise step fused): at light load a
+job then costs its stand-alone time instead of four batch builds and four
 dependent ticks.  As soon as two jobs overlap in a lane they share batched
 ticks again.
 

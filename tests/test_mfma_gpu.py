@@ -65,3 +65,29 @@ def test_grouped_launches_in_the_largest_class(cuda):
     for k, job in enumerate(jobs):
         assert np.array_equal(to_host(job["out"]), coracle.transform(field, "forward", xs[k])), f"job {k}"
     ntt_batch_destroy(h)
+
+
+@pytest.mark.parametrize("field", FIELDS)
+@pytest.mark.parametrize("log2n,radix,twiddles", [(12, 6, 1), (12, 7, 2), (14, 7, 1), (16, 8, 1), (18, 9, 1), (18, 6, 1),
+                                                  (19, 7, 2), (20, 8, 1), (22, 8, 1), (23, 8, 1), (24, 6, 1), (15, 8, 1)])
+def test_quotient_bridges(cuda, field, log2n, radix, twiddles):
+    """The chain with its transforms bridged, at each bridged radix, tile class
+    and number of passes (four at (24, 6)), and one plan without a bridge,
+    against the chain's stages run one by one."""
+    import torch
+
+    from paper_2509_22684_amd import Plan, quotient_pointwise
+
+    plan = Plan(field, log2n, log2_tile=10, log2_pass_radix=radix, twiddle_mode=twiddles)
+    xs = []
+    for v in range(3):
+        x = si.boundary_field_vector(field, 1 << 12, si.stream_seed(95, log2n, v))
+        xs.append(to_dev(np.tile(x, ((1 << log2n) >> 12, 1)), cuda))
+        # whole-vector structure, so that no column repeats another
+        xs[v] = plan.coset_forward(xs[v])
+    h = plan.quotient(*xs)
+    a, b, c = (plan.coset_forward(plan.inverse(x)) for x in xs)
+    e = torch.empty_like(a)
+    quotient_pointwise(plan.handle, a, b, c, e)
+    want = plan.coset_inverse(e)
+    assert torch.equal(h, want), f"{field} 2^{log2n} radix 2^{radix}"
