@@ -7,8 +7,8 @@ product and the coset inverse NTT: seven transforms).  `value` counts NTT
 elements per second over those seven transforms: 7 * 2^24 / step time.
 
 Also reported: the single forward NTT at 2^24 (elements/s); the roofline of
-the dominant kernel (the radix-256 pass kernel, timed per launch with HIP
-events on the stream it runs on); batched versus per-launch jobs/s for 64
+the dominant kernel (the matrix-core pass kernel at radix 256, timed per launch
+with HIP events on the stream it runs on); batched versus per-launch jobs/s for 64
 uneven forward NTTs over both fields; and the CPU oracle timed on a bounded
 sample on the host cores.
 
@@ -35,7 +35,8 @@ FIELD = "bls12_381_fr"
 PEAK_MAD_PER_S = 256 * 4 * 16 * 2.4e9
 PEAK_HBM_BYTES_PER_S = 8.0e12
 MADS_PER_FFMUL = 136  # 2 s^2 + s for s = 8 limbs (one CIOS/FIPS Montgomery product)
-KERNEL_SOURCES = ["paper_2509_22684_amd/csrc/field.hpp", "paper_2509_22684_amd/csrc/ntt_pass_impl.hpp"]
+KERNEL_SOURCES = ["paper_2509_22684_amd/csrc/field.hpp", "paper_2509_22684_amd/csrc/mfma_tables.hpp",
+                  "paper_2509_22684_amd/csrc/ntt_mfma_impl.hpp"]
 
 
 def kernel_hash() -> str:
@@ -49,7 +50,7 @@ def kernel_hash() -> str:
 def traffic_from_profile(khash: str):
     """HBM bytes per launch of the dominant kernel from the committed
     rocprofv3 counter summary, if it was taken on the current kernel source."""
-    path = os.path.join(ROOT, "profiles", "ntt_pass_r256_t10_2e24_traffic.json")
+    path = os.path.join(ROOT, "profiles", "mfma_pass_r256_2e24_traffic.json")
     if not os.path.exists(path):
         return None
     with open(path) as f:
@@ -62,7 +63,7 @@ def traffic_from_profile(khash: str):
 def valu_from_profile(khash: str):
     """VALU wave instructions per launch of the dominant kernel from the
     committed rocprofv3 counter summary, if taken on the current source."""
-    path = os.path.join(ROOT, "profiles", "ntt_pass_r256_t10_2e24_valu.json")
+    path = os.path.join(ROOT, "profiles", "mfma_pass_r256_2e24_valu.json")
     if not os.path.exists(path):
         return None
     with open(path) as f:
@@ -633,9 +634,11 @@ def main() -> int:
     peaks = peaks_leg(dev)
     mad_measured = peaks["mad_u64_u32"]["per_s"]
     roofline = {
+        # The passes' butterflies run on the matrix cores, so the VALU does
+        # fewer multiply-adds than the algorithm's count below; `achieved` is
+        # the algorithm's count over the time.
         "bound": "alu",
-        "kernel": f"ntt_pass_kernel<Bls12_381Fr, LOG_R={log_r}, LOG_TILE={plan.opts['log2_tile'] or 10}, "
-                  f"LOG_E={plan.opts['log2_radix'] or 2}>",
+        "kernel": f"mfma_pass_kernel<Bls12_381Fr, LOG_R={log_r}, LOG_TILE=10>",
         "achieved": achieved / 1e12,
         "peak": PEAK_MAD_PER_S / 1e12,
         "unit": "T MAD/s",
