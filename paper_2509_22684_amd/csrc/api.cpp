@@ -424,11 +424,11 @@ int validate_input(ntt_plan* p, const void* x, hipStream_t s) {
 // safe because the last pass writes exactly the elements each tile reads.
 // `swapped`: pass 0 wrote `out`, and the passes after it alternate the other
 // way.
-zk::PassArgs make_pass_args(const ntt_plan* p, Kind kind, size_t k, const void* in, void* out, void* work,
-                            bool swapped = false) {
+zk::PassLaunch make_pass_args(const ntt_plan* p, Kind kind, size_t k, const void* in, void* out, void* work,
+                              bool swapped = false) {
   const size_t P = p->passes.size();
   const PassDesc& d = p->passes[k];
-  zk::PassArgs a{};
+  zk::PassLaunch a{};
   const size_t turn = swapped ? k + 1 : k;
   a.in = static_cast<const Fe*>(k == 0 ? in : (turn % 2 == 1 ? work : out));
   a.out = static_cast<Fe*>(k + 1 == P ? out : (turn % 2 == 0 ? work : out));
@@ -479,7 +479,7 @@ int run_transform(const ntt_plan* p, Kind kind, const void* in, void* out, void*
       if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
     }
     const PassDesc& d = p->passes[k];
-    const zk::PassArgs a = make_pass_args(p, kind, k, in, out, work);
+    const zk::PassLaunch a = make_pass_args(p, kind, k, in, out, work);
     hipError_t e = zk::launch_pass(p->kfield, d.log_r, d.log_tile, a, s);
     if (e != hipSuccess) return hip_fail(e, "NTT pass launch");
   }
@@ -502,11 +502,11 @@ int run_grouped(const ntt_plan* p, Kind kind, const Vectors* v, uint32_t jobs, s
                 bool swapped, Adjust adjust) {
   for (size_t k = first; k < end; ++k) {
     const PassDesc& d = p->passes[k];
-    zk::PassArgs a = make_pass_args(p, kind, k, v[0].in, v[0].out, v[0].work, swapped);
+    zk::PassLaunch a = make_pass_args(p, kind, k, v[0].in, v[0].out, v[0].work, swapped);
     a.grp_jobs = jobs;
     adjust(a, v[0]);
     for (uint32_t j = 1; j < jobs; ++j) {
-      zk::PassArgs b = make_pass_args(p, kind, k, v[j].in, v[j].out, v[j].work, swapped);
+      zk::PassLaunch b = make_pass_args(p, kind, k, v[j].in, v[j].out, v[j].work, swapped);
       adjust(b, v[j]);
       a.few_in[j - 1] = b.in;
       a.few_out[j - 1] = b.out;
@@ -518,7 +518,7 @@ int run_grouped(const ntt_plan* p, Kind kind, const Vectors* v, uint32_t jobs, s
 }
 int run_grouped(const ntt_plan* p, Kind kind, const Vectors* v, uint32_t jobs, size_t first, size_t end, hipStream_t s,
                 bool swapped = false) {
-  return run_grouped(p, kind, v, jobs, first, end, s, swapped, [](zk::PassArgs&, const Vectors&) {});
+  return run_grouped(p, kind, v, jobs, first, end, s, swapped, [](zk::PassLaunch&, const Vectors&) {});
 }
 
 size_t workspace_elems(const ntt_plan* p) { return p->passes.size() >= 2 ? p->n : 0; }
@@ -551,7 +551,7 @@ int run_to_coset(const ntt_plan* p, const Vectors* v, uint32_t jobs, hipStream_t
   if (int rc = run_grouped(p, kInverseRaw, v, jobs, 0, P - 1, s)) return rc;
   // the bridge writes whichever of out and work it doesn't read
   *swapped = P % 2 == 0;
-  auto bridge = [&](zk::PassArgs& a, const Vectors& x) {
+  auto bridge = [&](zk::PassLaunch& a, const Vectors& x) {
     a.flags |= zk::kPassBridge | zk::kPassPreTable;
     a.pre_table = p->inv_to_coset;
     a.out = static_cast<Fe*>(*swapped ? x.out : x.work);
@@ -568,7 +568,7 @@ int run_to_quotient(const ntt_plan* p, const Vectors& c, const Fe* a, const Fe* 
   const size_t P = p->passes.size();
   const Vectors h{c.out, c.out, c.work};
   const bool bridge = bridges(p);
-  auto pointwise = [&](zk::PassArgs& x, const Vectors& v) {
+  auto pointwise = [&](zk::PassLaunch& x, const Vectors& v) {
     x.flags |= zk::kPassPostPointwise;
     x.pw_a = a;
     x.pw_b = b;
@@ -930,7 +930,7 @@ struct DirectWork {
   const void* in2;
   const void* in3;
   void* out;
-  std::vector<zk::PassArgs> pass;  // grouped transforms
+  std::vector<zk::PassLaunch> pass;  // grouped transforms
   std::vector<size_t> ptr_off;     // per pass: offset of its in pointers in the batch's pointer array
   size_t lane = 0;                 // side stream it runs on
 };
@@ -1413,7 +1413,7 @@ int batch_build(ntt_batch** out, const ntt_batch_job* specs, int njobs, bool cap
     DirectWork d{p, false, nullptr, nullptr, nullptr, nullptr, {}, {}};
     for (size_t q = 0; q < p->passes.size(); ++q) {
       const ntt_batch_job& s0 = specs[g[0]];
-      zk::PassArgs a = make_pass_args(p, kinds[g[0]], q, s0.in, s0.out, s0.work);
+      zk::PassLaunch a = make_pass_args(p, kinds[g[0]], q, s0.in, s0.out, s0.work);
       a.grp_jobs = (uint32_t)g.size();
       a.log_grp_tiles = p->log_n - (uint32_t)p->passes[q].log_tile;
       d.ptr_off.push_back(ptrs.size());

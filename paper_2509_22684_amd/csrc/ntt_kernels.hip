@@ -10,13 +10,13 @@
 
 namespace zk {
 
-hipError_t launch_pass_bls(int log_r, const PassArgs& a, hipStream_t s);
-hipError_t launch_pass_bn(int log_r, const PassArgs& a, hipStream_t s);
-hipError_t launch_pass_b377(int log_r, const PassArgs& a, hipStream_t s);
-hipError_t launch_pass_bls_f64_e2(int log_r, int log_tile, const PassArgs& a, hipStream_t s);
-hipError_t launch_mfma_bls(int log_r, const PassArgs& a, hipStream_t s);
-hipError_t launch_mfma_bn(int log_r, const PassArgs& a, hipStream_t s);
-hipError_t launch_mfma_b377(int log_r, const PassArgs& a, hipStream_t s);
+hipError_t launch_pass_bls(int log_r, const PassLaunch& a, hipStream_t s);
+hipError_t launch_pass_bn(int log_r, const PassLaunch& a, hipStream_t s);
+hipError_t launch_pass_b377(int log_r, const PassLaunch& a, hipStream_t s);
+hipError_t launch_pass_bls_f64_e2(int log_r, int log_tile, const PassLaunch& a, hipStream_t s);
+hipError_t launch_mfma_bls(int log_r, const PassLaunch& a, hipStream_t s);
+hipError_t launch_mfma_bn(int log_r, const PassLaunch& a, hipStream_t s);
+hipError_t launch_mfma_b377(int log_r, const PassLaunch& a, hipStream_t s);
 
 namespace {
 using detail::load_fe;
@@ -82,7 +82,7 @@ inline uint32_t blocks_for(uint64_t n, uint32_t per) { return (uint32_t)((n + pe
 
 }  // namespace
 
-hipError_t launch_pass(int field, int log_r, int log_tile, const PassArgs& a, hipStream_t s) {
+hipError_t launch_pass(int field, int log_r, int log_tile, const PassLaunch& a, hipStream_t s) {
   if (field == kFieldBls12_381Fp64) return launch_pass_bls_f64_e2(log_r, log_tile, a, s);
   const bool tiny = (uint32_t)log_r == a.log_n && log_r <= kTinyLog;
   if (!tiny && !mfma_supported(log_r, a.log_n)) return hipErrorInvalidValue;

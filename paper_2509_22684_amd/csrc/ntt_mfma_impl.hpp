@@ -409,7 +409,7 @@ __device__ const DigitTable digit_table = make_digit_table<F>();
 template <class F, int LOG_R, int LOG_TILE, int LOG_THREADS, bool BRIDGE>
 __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS),
                                   (Shape<LOG_R, LOG_TILE, LOG_THREADS>::MIN_WAVES))
-    mfma_pass_kernel(PassArgs a) {
+    mfma_pass_kernel(PassLaunch a) {
   using S = Shape<LOG_R, LOG_TILE, LOG_THREADS>;
   using Rd = typename S::Rd;
   __shared__ U32x4 lds[S::LDS_DATA + S::LDS_A];
@@ -577,9 +577,9 @@ __global__ void __launch_bounds__((Shape<LOG_R, LOG_TILE, LOG_THREADS>::THREADS)
 }
 
 template <class F, bool BRIDGE, int LOG_R, int LOG_TILE, int LOG_THREADS>
-hipError_t launch_one(const PassArgs& a0, hipStream_t s) {
+hipError_t launch_one(const PassLaunch& a0, hipStream_t s) {
   using S = Shape<LOG_R, LOG_TILE, LOG_THREADS>;
-  PassArgs a = a0;
+  PassLaunch a = a0;
   a.log_grp_tiles = a.log_n - LOG_TILE;
   const uint64_t tiles = ((1ull << a.log_n) >> LOG_TILE) * (a.grp_jobs ? a.grp_jobs : 1u);
   hipLaunchKernelGGL((mfma_pass_kernel<F, LOG_R, LOG_TILE, LOG_THREADS, BRIDGE>), dim3((uint32_t)tiles),
@@ -606,7 +606,7 @@ inline bool four_per_lane(uint64_t elements) {
 
 // Passes of multi-pass transforms (radix 2^3 .. 2^9; bridges 2^6 .. 2^9).
 template <class F, bool BRIDGE>
-hipError_t dispatch_multi(int log_r, const PassArgs& a, hipStream_t s) {
+hipError_t dispatch_multi(int log_r, const PassLaunch& a, hipStream_t s) {
   const uint64_t total = (a.grp_jobs ? a.grp_jobs : 1ull) << a.log_n;
   if (total >> kTwoLog && a.log_n >= 10 && four_per_lane(total)) {
     if constexpr (!BRIDGE) {
@@ -659,7 +659,7 @@ hipError_t dispatch_multi(int log_r, const PassArgs& a, hipStream_t s) {
 // A pass of a multi-pass transform, or a transform of 2^8 to 2^11 points in
 // one tile.  Keep in step with mfma_supported() and bridge_supported().
 template <class F>
-hipError_t dispatch(int log_r, const PassArgs& a, hipStream_t s) {
+hipError_t dispatch(int log_r, const PassLaunch& a, hipStream_t s) {
   if ((uint32_t)log_r == a.log_n) {
     switch (log_r) {
       case 8: return launch_one<F, false, 8, 8, 8>(a, s);

@@ -2,7 +2,7 @@
 #include "ntt_pass_impl.hpp"
 
 namespace zk {
-hipError_t launch_pass_b377(int log_r, const PassArgs& a, hipStream_t s) {
+hipError_t launch_pass_b377(int log_r, const PassLaunch& a, hipStream_t s) {
   return detail::dispatch_tiny<Bls12_377Fr>(log_r, a, s);
 }
 }  // namespace zk

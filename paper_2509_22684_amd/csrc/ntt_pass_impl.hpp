@@ -280,7 +280,7 @@ __device__ __forceinline__ void tile_round(Fe (&v)[N], Fe* lds, const Fe* __rest
 // (same loads and arithmetic) but store nothing, so a workgroup wider than
 // the tile still reaches every barrier.  `lds` holds LDS_SLOTS elements.
 template <class F, int LOG_R, int LOG_TILE, int LOG_E>
-__device__ __forceinline__ void pass_tile(const PassArgs& a, uint64_t tile, Fe* lds, uint32_t t, bool writer) {
+__device__ __forceinline__ void pass_tile(const PassLaunch& a, uint64_t tile, Fe* lds, uint32_t t, bool writer) {
   using S = PassShape<LOG_R, LOG_TILE, LOG_E>;
   // Thread t of the tile handles column c and slot q.  Lanes of a wave take
   // the J columns fastest (so global accesses stay in J x 32-byte runs); the
@@ -412,7 +412,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, uint64_t tile, Fe* 
 template <class F, int LOG_R, int LOG_TILE, int LOG_E>
 __global__ void __launch_bounds__((PassShape<LOG_R, LOG_TILE, LOG_E>::THREADS),
                                   (PassShape<LOG_R, LOG_TILE, LOG_E>::MIN_WAVES))
-    ntt_pass_kernel(PassArgs a) {
+    ntt_pass_kernel(PassLaunch a) {
   using S = PassShape<LOG_R, LOG_TILE, LOG_E>;
   __shared__ Fe lds[S::LDS_SLOTS];
   const uint32_t tile = pass_tile_index(a, blockIdx.x);
@@ -426,9 +426,9 @@ namespace zk {
 namespace detail {
 
 template <class F, int LOG_R, int LOG_TILE, int LOG_E>
-hipError_t launch_one(const PassArgs& a0, hipStream_t s) {
+hipError_t launch_one(const PassLaunch& a0, hipStream_t s) {
   using S = PassShape<LOG_R, LOG_TILE, LOG_E>;
-  PassArgs a = a0;
+  PassLaunch a = a0;
   a.log_grp_tiles = a.log_n - LOG_TILE;
   const uint64_t tiles = ((1ull << a.log_n) >> LOG_TILE) * (a.grp_jobs ? a.grp_jobs : 1u);
   hipLaunchKernelGGL((ntt_pass_kernel<F, LOG_R, LOG_TILE, LOG_E>), dim3((uint32_t)tiles), dim3(S::THREADS), 0, s, a);
@@ -440,7 +440,7 @@ hipError_t launch_one(const PassArgs& a0, hipStream_t s) {
 // single-pass transforms of up to 2^11 points held in one tile.  Keep in step
 // with fp64_shape_supported().
 template <class F, int LOG_E>
-hipError_t dispatch_shape(int log_r, int log_tile, const PassArgs& a, hipStream_t s) {
+hipError_t dispatch_shape(int log_r, int log_tile, const PassLaunch& a, hipStream_t s) {
   if (log_tile == 8 && log_r < 8) {
     switch (log_r) {
       case 3: return launch_one<F, 3, 8, LOG_E>(a, s);
@@ -498,7 +498,7 @@ hipError_t dispatch_shape(int log_r, int log_tile, const PassArgs& a, hipStream_
 // Whole transforms of at most 2^kTinyLog points, radix-2 rounds (a lone
 // workgroup: more threads per tile shorten it).
 template <class F>
-hipError_t dispatch_tiny(int log_r, const PassArgs& a, hipStream_t s) {
+hipError_t dispatch_tiny(int log_r, const PassLaunch& a, hipStream_t s) {
   switch (log_r) {
     case 0: return launch_one<F, 0, 0, 1>(a, s);
     case 1: return launch_one<F, 1, 1, 1>(a, s);
