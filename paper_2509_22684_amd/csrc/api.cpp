@@ -32,6 +32,7 @@
 
 #include "../../include/zkntt.h"
 #include "field.hpp"
+#include "host_rules.hpp"
 #include "msm.hpp"
 #include "ntt_batch.hpp"
 #include "ntt_kernels.hpp"
@@ -1803,11 +1804,7 @@ int msm_bases_create(msm_bases** out, const void* d_points, uint64_t n, uint32_t
   // group below 2^16
   b->per_group = (uint32_t)std::min<uint64_t>(n, 65535u / (uint32_t)windows);
   b->groups = (uint32_t)((n + b->per_group - 1) / b->per_group);
-  // Fewest entries per lane: a mixed addition in a lane takes about twice as
-  // long as the addition of a run's head by a quad, so runs of about an eighth
-  // of a bucket, and no fewer than eight entries, end soonest when there are
-  // lanes to spare.
-  b->kmin = (uint32_t)std::max<uint64_t>(8, ((uint64_t)windows * n) >> (c + 3));
+  b->kmin = zk::rules::msm_min_run((uint64_t)windows, n, c);
   // accumulation lanes: the resident ones, fewer when the entries are few
   e = zk::msm::accumulate_lanes(&b->lanes);
   if (e != hipSuccess) {
