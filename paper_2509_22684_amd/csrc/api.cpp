@@ -1297,25 +1297,25 @@ int batch_build(ntt_batch** out, const ntt_batch_job* specs, int njobs, bool cap
   std::vector<bool> direct(njobs, false);
   for (int k = 0; k < njobs; ++k)
     if (jobs[k].kind == zk::kJobPointwise) direct[k] = all_direct || load(k) * zk::kXcds > total;
-  constexpr double kLaunchUs = 4.0;      // gap between dependent launches
-  constexpr double kPassUs = 6.0;        // shortest pass
-  constexpr double kUsPerElem = 33.0 / (1 << 20);  // a pass that fills the chip, per element
-  constexpr double kBatchItemUs = 70.0;  // one 2^11-element item of the persistent kernel
   const double batch_slots = (double)cus * zk::batch_workgroups_per_cu();
+  bool all_tiny = true;  // every transform is one workgroup of the register kernels
+  for (const std::vector<int>& g : groups) all_tiny = all_tiny && specs[g[0]].plan->log_n <= (uint32_t)zk::kTinyLog;
+  auto pass_us = [&](const ntt_plan* p, uint64_t count) {
+    return zk::rules::grouped_pass_us(p->log_n, all_tiny, count, cus);
+  };
   const size_t G = groups.size();
   std::vector<double> grouped_us(G), group_items(G), alone_us(G);
   for (size_t g = 0; g < G; ++g) {
     const ntt_plan* p = specs[groups[g][0]].plan;
-    grouped_us[g] = (double)p->passes.size() *
-                    (kLaunchUs + std::max(kPassUs, kUsPerElem * (double)p->n * (double)groups[g].size()));
+    grouped_us[g] = (double)p->passes.size() * pass_us(p, groups[g].size());
     group_items[g] = (double)(load(groups[g][0]) * groups[g].size());
-    alone_us[g] = (double)load(groups[g][0]) * kBatchItemUs / (batch_slots / zk::kXcds);
+    alone_us[g] = zk::rules::persistent_us((double)load(groups[g][0]), batch_slots / zk::kXcds);
   }
   double other_items = 0, other_alone = 0;  // persistent work outside the groups
   for (int k = 0; k < njobs; ++k)
     if (jobs[k].kind == zk::kJobPointwise && !direct[k]) {
       other_items += (double)load(k);
-      other_alone = std::max(other_alone, (double)load(k) * kBatchItemUs / (batch_slots / zk::kXcds));
+      other_alone = std::max(other_alone, zk::rules::persistent_us((double)load(k), batch_slots / zk::kXcds));
     }
   std::vector<bool> moved(G, false);
   auto estimate = [&](size_t flip) {
@@ -1328,7 +1328,7 @@ int batch_build(ntt_batch** out, const ntt_batch_job* specs, int njobs, bool cap
         alone = std::max(alone, alone_us[g]);
       }
     }
-    return t + (it > 0 ? std::max(it * kBatchItemUs / batch_slots, alone) : 0.0);
+    return t + (it > 0 ? std::max(zk::rules::persistent_us(it, batch_slots), alone) : 0.0);
   };
   if (all_direct) std::fill(moved.begin(), moved.end(), true);
   for (double best = estimate(G); !all_direct;) {
@@ -1464,12 +1464,11 @@ int batch_build(ntt_batch** out, const ntt_batch_job* specs, int njobs, bool cap
       std::vector<double> lane_us(nsides, 0.0);
       for (const DirectWork& d : b->direct) {
         if (d.pointwise) continue;
-        const double elems = (double)d.plan->n * std::max<uint32_t>(1, d.pass[0].grp_jobs);
-        lane_us[d.lane] += (double)d.pass.size() * (kLaunchUs + std::max(kPassUs, kUsPerElem * elems));
+        lane_us[d.lane] += (double)d.pass.size() * pass_us(d.plan, std::max<uint32_t>(1, d.pass[0].grp_jobs));
       }
       const double longest = *std::max_element(lane_us.begin(), lane_us.end());
       const uint32_t half = (uint32_t)std::max(1, cus / 2);
-      if ((double)items.size() * kBatchItemUs / half <= 2.0 * longest)
+      if (zk::rules::persistent_us((double)items.size(), half) <= 2.0 * longest)
         b->grid = std::min<uint32_t>(b->grid, half);
     }
     b->sides.assign(nsides, nullptr);

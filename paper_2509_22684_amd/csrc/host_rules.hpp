@@ -21,5 +21,32 @@ inline uint32_t msm_min_run(uint64_t windows, uint64_t n, int c) {
   return (uint32_t)std::min<uint64_t>(32, std::max<uint64_t>(8, eighth));
 }
 
+// Batches: estimated times of the two ways to run a group of transforms, in
+// microseconds; only their order matters.
+constexpr double kLaunchUs = 4.0;                // gap between dependent launches
+constexpr double kPassUs = 6.0;                  // shortest matrix-core pass
+constexpr double kUsPerElem = 33.0 / (1 << 20);  // a pass that fills the chip, per element
+constexpr double kBatchItemUs = 70.0;            // one 2^11-element item of the persistent kernel
+
+// One pass of `jobs` transforms of 2^log_n points as one launch.  `whole`:
+// whole transforms of at most 2^7 points, a workgroup of the register kernels
+// each, 4 per CU at once and shorter with the size (40 us at 2^10 points), in
+// a batch that holds nothing larger.  These have no floor of kPassUs: the
+// persistent kernel's estimate, which has no floor either, would win, and 64
+// transforms of 2^2 (2^6) points take 13 (18) us as a launch and 34 (43) us in
+// the persistent kernel.  Beside larger transforms, where the launch does not
+// save the persistent kernel, they are better left to it (40 transforms of 2^2
+// and 40 of 2^12 points: 59 us, and 67 with both as launches).
+inline double grouped_pass_us(uint32_t log_n, bool whole, uint64_t jobs, int cus) {
+  if (whole) {
+    const uint64_t rounds = (jobs + 4u * (uint64_t)cus - 1) / (4u * (uint64_t)cus);
+    return kLaunchUs + (double)rounds * 40.0 * (double)(1u << log_n) / 1024.0;
+  }
+  return kLaunchUs + std::max(kPassUs, kUsPerElem * (double)(1ull << log_n) * (double)jobs);
+}
+
+// The persistent kernel over `items` items with room for `slots` at once.
+inline double persistent_us(double items, double slots) { return items * kBatchItemUs / slots; }
+
 }  // namespace rules
 }  // namespace zk

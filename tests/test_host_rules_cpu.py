@@ -33,3 +33,16 @@ def test_msm_runs_are_never_a_long_serial_chain(tmp_path):
     for (c, n), run in zip(cases, got):
         eighth = (-(-255 // c) * n) >> (c + 3)
         assert run == min(32, max(8, eighth)), f"c {c}, n {n}"
+
+
+def test_tiny_transforms_in_numbers_run_as_one_launch(tmp_path):
+    """64 transforms of up to 2^6 points, an item each (two workgroups on each of
+    256 CUs) are estimated, and measured, shorter as one launch; two of them are
+    left to the persistent kernel.  A matrix-core pass has its floor."""
+    sizes = range(2, 7)
+    group = evaluate(tmp_path, [f"grouped_pass_us({k}, true, {jobs}, 256)" for jobs in (64, 2) for k in sizes])
+    both = evaluate(tmp_path, ["persistent_us(64, 512)", "persistent_us(2, 512)"])
+    assert all(t < both[0] for t in group[:5])
+    assert all(t > both[1] for t in group[5:])
+    floor, full = evaluate(tmp_path, ["grouped_pass_us(12, false, 1, 256)", "grouped_pass_us(18, false, 16, 256)"])
+    assert floor == 10.0 and full == 4.0 + 4 * 33.0
