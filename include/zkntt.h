@@ -217,10 +217,10 @@ int zk_copy_to_host(void *host_dst, const void *dev_src, size_t bytes, void *str
  * launch per pass for all jobs of the group) over the whole chip; the choice
  * follows a time estimate made when the batch is created.  A pointwise job
  * larger than an eighth of the batch runs as its own launch the same way.
- * Such launches go to up to four side streams of the batch, forked from the
- * launch stream before the persistent kernel and joined into it after (in
- * the graph: parallel branches), so the call still completes in stream
- * order on the stream it was given.
+ * Such launches go to up to four side streams of the batch (three in a batch
+ * without a graph), forked from the launch stream before the persistent
+ * kernel and joined into it after (in the graph: parallel branches), so the
+ * call still completes in stream order on the stream it was given.
  * Every tile is computed exactly as in the stand-alone transform, so results
  * are byte-identical to ntt_forward.
  *

@@ -1431,12 +1431,10 @@ int batch_build(ntt_batch** out, const ntt_batch_job* specs, int njobs, bool cap
   // of that when its items can wait).
   const bool beside = !b->direct.empty() && !items.empty();
   b->grid = (uint32_t)std::min<size_t>(items.size(), (size_t)cus * (beside ? 1 : zk::batch_workgroups_per_cu()));
-  // Direct work goes to up to kSideStreams side streams, dealt largest first
-  // (by tiles over all passes) to the least loaded, so that groups too small
-  // to fill the chip alone run at the same time (64-job batch: 0.411 ms with
-  // three, 0.390 with four, 0.397 with six).
-  constexpr size_t kSideStreams = 4;
-  const size_t nsides = std::min(kSideStreams, b->direct.size());
+  // Direct work goes to a few side streams, dealt largest first (by tiles over
+  // all passes) to the least loaded, so that groups too small to fill the chip
+  // alone run at the same time.
+  const size_t nsides = std::min(zk::rules::side_streams(capture), b->direct.size());
   if (nsides > 1 || beside) {
     std::vector<size_t> order(b->direct.size());
     std::vector<uint64_t> work(b->direct.size(), 0), lane_load(nsides, 0);

@@ -2,6 +2,7 @@
 // without HIP, so that they can be checked on any machine.
 #pragma once
 #include <algorithm>
+#include <cstddef>
 #include <cstdint>
 
 namespace zk {
@@ -47,6 +48,15 @@ inline double grouped_pass_us(uint32_t log_n, bool whole, uint64_t jobs, int cus
 
 // The persistent kernel over `items` items with room for `slots` at once.
 inline double persistent_us(double items, double slots) { return items * kBatchItemUs / slots; }
+
+// Side streams a batch's direct work is dealt to, at most.  In a graph they
+// are parallel branches, and a fourth costs nothing: the 64-job batch takes
+// 0.411 ms with three, 0.390 with four, 0.397 with six.  A batch launched
+// without one pays for each on the host, at every launch, with a wait, a
+// record and another wait, and its launches come later (five transforms of 2^8
+// points in five launches 89 us with three, 105 with four; 64 transforms of
+// 2^10 to 2^18 points, all as launches, 413 and 501).
+inline size_t side_streams(bool graph) { return graph ? 4 : 3; }
 
 }  // namespace rules
 }  // namespace zk

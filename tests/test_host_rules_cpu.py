@@ -46,3 +46,9 @@ def test_tiny_transforms_in_numbers_run_as_one_launch(tmp_path):
     assert all(t > both[1] for t in group[5:])
     floor, full = evaluate(tmp_path, ["grouped_pass_us(12, false, 1, 256)", "grouped_pass_us(18, false, 16, 256)"])
     assert floor == 10.0 and full == 4.0 + 4 * 33.0
+
+
+def test_side_streams_by_the_way_a_batch_is_launched(tmp_path):
+    """A graph's branches are free; without a graph each stream is paid for at
+    every launch."""
+    assert evaluate(tmp_path, ["side_streams(true)", "side_streams(false)"]) == [4, 3]
