@@ -8,6 +8,18 @@
 namespace zk {
 namespace rules {
 
+// Whole transforms of 2^log_n points in one tile each, `elements` elements in
+// the launch: true where the register kernels take them.  Up to 2^7 points
+// always.  From 2^8 to 2^10 points the matrix-core kernels hold one element
+// per lane, for the latency of a launch that does not fill the chip; one that
+// does is shorter in the register kernels, four per lane (matrix cores and
+// registers, us: 16,384 of 2^8 points 174 and 154, 4,096 of them 53 and 53;
+// 8,192 of 2^9 185 and 176, 2,048 of them 57 and 60; 4,096 of 2^10 238 and
+// 202, 1,024 of them 72 and 69, 512 of them 41 and 44).
+constexpr bool register_whole(uint32_t log_n, uint64_t elements) {
+  return log_n <= 7 || (log_n <= 10 && (elements >> (log_n == 10 ? 20 : 21)) != 0);
+}
+
 // MSM: fewest sorted entries per accumulation lane, for `windows` windows of c
 // bits and n points.  A mixed addition in a lane takes about twice as long as
 // the addition of a run's head by a quad, so where lanes are to spare runs of

@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "field_f64.hpp"
+#include "host_rules.hpp"
 #include "ntt_kernels.hpp"
 #include "ntt_pass_impl.hpp"
 
@@ -82,13 +83,17 @@ inline uint32_t blocks_for(uint64_t n, uint32_t per) { return (uint32_t)((n + pe
 
 }  // namespace
 
+static_assert(rules::register_whole(kTinyLog, 1) && !rules::register_whole(kTinyLog + 1, 1),
+              "the register kernels take what mfma_supported() leaves");
+
 hipError_t launch_pass(int field, int log_r, int log_tile, const PassLaunch& a, hipStream_t s) {
   if (field == kFieldBls12_381Fp64) return launch_pass_bls_f64_e2(log_r, log_tile, a, s);
-  const bool tiny = (uint32_t)log_r == a.log_n && log_r <= kTinyLog;
-  if (!tiny && !mfma_supported(log_r, a.log_n)) return hipErrorInvalidValue;
-  if (field == Bls12_381Fr::ID) return tiny ? launch_pass_bls(log_r, a, s) : launch_mfma_bls(log_r, a, s);
-  if (field == Bn254Fr::ID) return tiny ? launch_pass_bn(log_r, a, s) : launch_mfma_bn(log_r, a, s);
-  if (field == Bls12_377Fr::ID) return tiny ? launch_pass_b377(log_r, a, s) : launch_mfma_b377(log_r, a, s);
+  const uint64_t elements = (a.grp_jobs ? a.grp_jobs : 1ull) << a.log_n;
+  const bool reg = (uint32_t)log_r == a.log_n && rules::register_whole(a.log_n, elements);
+  if (!reg && !mfma_supported(log_r, a.log_n)) return hipErrorInvalidValue;
+  if (field == Bls12_381Fr::ID) return reg ? launch_pass_bls(log_r, a, s) : launch_mfma_bls(log_r, a, s);
+  if (field == Bn254Fr::ID) return reg ? launch_pass_bn(log_r, a, s) : launch_mfma_bn(log_r, a, s);
+  if (field == Bls12_377Fr::ID) return reg ? launch_pass_b377(log_r, a, s) : launch_mfma_b377(log_r, a, s);
   return hipErrorInvalidValue;
 }
 

@@ -3,6 +3,6 @@
 
 namespace zk {
 hipError_t launch_pass_bls(int log_r, const PassLaunch& a, hipStream_t s) {
-  return detail::dispatch_tiny<Bls12_381Fr>(log_r, a, s);
+  return detail::dispatch_registers<Bls12_381Fr>(log_r, a, s);
 }
 }  // namespace zk

@@ -3,6 +3,6 @@
 
 namespace zk {
 hipError_t launch_pass_bn(int log_r, const PassLaunch& a, hipStream_t s) {
-  return detail::dispatch_tiny<Bn254Fr>(log_r, a, s);
+  return detail::dispatch_registers<Bn254Fr>(log_r, a, s);
 }
 }  // namespace zk

@@ -495,10 +495,11 @@ hipError_t dispatch_shape(int log_r, int log_tile, const PassLaunch& a, hipStrea
   return hipErrorInvalidValue;
 }
 
-// Whole transforms of at most 2^kTinyLog points, radix-2 rounds (a lone
-// workgroup: more threads per tile shorten it).
+// Whole transforms (rules::register_whole): radix-2 rounds up to 2^kTinyLog
+// points (a lone workgroup: more threads per tile shorten it), radix-4 above
+// (the chip is full: fewer instructions per element).
 template <class F>
-hipError_t dispatch_tiny(int log_r, const PassLaunch& a, hipStream_t s) {
+hipError_t dispatch_registers(int log_r, const PassLaunch& a, hipStream_t s) {
   switch (log_r) {
     case 0: return launch_one<F, 0, 0, 1>(a, s);
     case 1: return launch_one<F, 1, 1, 1>(a, s);
@@ -508,6 +509,9 @@ hipError_t dispatch_tiny(int log_r, const PassLaunch& a, hipStream_t s) {
     case 5: return launch_one<F, 5, 5, 1>(a, s);
     case 6: return launch_one<F, 6, 6, 1>(a, s);
     case 7: return launch_one<F, 7, 7, 1>(a, s);
+    case 8: return launch_one<F, 8, 8, 2>(a, s);
+    case 9: return launch_one<F, 9, 9, 2>(a, s);
+    case 10: return launch_one<F, 10, 10, 2>(a, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -52,3 +52,12 @@ def test_side_streams_by_the_way_a_batch_is_launched(tmp_path):
     """A graph's branches are free; without a graph each stream is paid for at
     every launch."""
     assert evaluate(tmp_path, ["side_streams(true)", "side_streams(false)"]) == [4, 3]
+
+
+def test_whole_transforms_of_the_register_kernels(tmp_path):
+    """Up to 2^7 points always, 2^8 to 2^10 in launches that fill the chip, 2^11
+    never."""
+    cases = [(0, 1, 1), (7, 1 << 7, 1), (7, 1 << 22, 1), (8, 1 << 8, 0), (8, (1 << 21) - (1 << 8), 0), (8, 1 << 21, 1),
+             (9, 1 << 20, 0), (9, 1 << 21, 1), (10, 1 << 19, 0), (10, 1 << 20, 1), (11, 1 << 24, 0)]
+    got = evaluate(tmp_path, [f"register_whole({n}, {e}ull)" for n, e, _ in cases])
+    assert got == [c[2] for c in cases]
