@@ -193,7 +193,8 @@ std::vector<int> split_passes(uint32_t log_n, const ntt_plan_opts& o) {
   }
   uint32_t max_log_r = o.log2_pass_radix;
   if (o.flags & ZK_FLAG_FFMUL_FP64) max_log_r = std::min(max_log_r, o.log2_tile - 1);
-  const int P = (int)((log_n + max_log_r - 1) / max_log_r);
+  // more than the tile's points take two passes, also where one could hold them
+  const int P = std::max(2, (int)((log_n + max_log_r - 1) / max_log_r));
   const int base = (int)log_n / P, extra = (int)log_n % P;
   for (int k = 0; k < P; ++k) r.push_back(base + (k < extra ? 1 : 0));
   if (P == 3 && extra) r[0] = r[2] = base + (extra == 2), r[1] = base + (extra == 1);
