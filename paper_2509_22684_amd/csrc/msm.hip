@@ -641,7 +641,7 @@ __global__ void __launch_bounds__(kBigThreads) big_item_kernel(const uint32_t* _
                                                                uint32_t lanes, uint32_t kmin,
                                                                const uint32_t* __restrict__ head,
                                                                const uint32_t* __restrict__ tail, BigLists big) {
-  __shared__ uint32_t sh[kBigThreads / 4 * kAccWords];
+  __shared__ alignas(16) uint32_t sh[kBigThreads / 4 * kAccWords];
   const uint32_t items = big.count[1], g = threadIdx.x / 4;
   const uint32_t E = offsets[nb];
   const uint32_t K = lane_span(E, lanes, kmin);
@@ -665,7 +665,7 @@ __global__ void __launch_bounds__(kBigThreads) big_item_kernel(const uint32_t* _
 
 // The listed buckets from their items' sums.
 __global__ void __launch_bounds__(kBigThreads) big_bucket_kernel(BigLists big, uint32_t* __restrict__ buckets) {
-  __shared__ uint32_t sh[kBigThreads / 4 * kAccWords];
+  __shared__ alignas(16) uint32_t sh[kBigThreads / 4 * kAccWords];
   const uint32_t n = big.count[0], g = threadIdx.x / 4;
   for (uint32_t k = blockIdx.x; k < n; k += gridDim.x) {
     const uint4 b = big.bucket[k];
@@ -720,7 +720,7 @@ __device__ __forceinline__ Fq tree_lists(const uint32_t* __restrict__ in, int le
 // out[t nblk + k] (t = 0: S, 1 + b: G_b).
 __global__ void __launch_bounds__(kTreeThreads) tree_kernel(const uint32_t* __restrict__ buckets, int levels,
                                                             uint32_t* __restrict__ out) {
-  __shared__ uint32_t sh[2 * (kTreeThreads / 4) * kAccWords];
+  __shared__ alignas(16) uint32_t sh[2 * (kTreeThreads / 4) * kAccWords];
   const uint32_t g = threadIdx.x / 4;
   const Fq r = tree_lists(buckets + ((uint64_t)blockIdx.x << levels) * kAccWords, levels, true, sh);
   if (g <= (uint32_t)levels) q_store(out, (uint64_t)g * gridDim.x + blockIdx.x, r);
@@ -731,7 +731,7 @@ __global__ void __launch_bounds__(kTreeThreads) tree_kernel(const uint32_t* __re
 // those above the first kernel's `below`.
 __global__ void __launch_bounds__(kTreeThreads) tree_top_kernel(const uint32_t* __restrict__ in, int levels, int below,
                                                                 uint32_t* __restrict__ G) {
-  __shared__ uint32_t sh[2 * (kTreeThreads / 4) * kAccWords];
+  __shared__ alignas(16) uint32_t sh[2 * (kTreeThreads / 4) * kAccWords];
   const uint32_t g = threadIdx.x / 4, t = blockIdx.x;
   const Fq r = tree_lists(in + ((uint64_t)t << levels) * kAccWords, levels, t == 0, sh);
   if (t > 0) {
@@ -744,7 +744,7 @@ __global__ void __launch_bounds__(kTreeThreads) tree_top_kernel(const uint32_t* 
 // result = sum_b 2^b G_b (b < c <= 16): quad b doubles G_b b times, then a
 // tree sums the c scaled points.
 __global__ void __launch_bounds__(64) final_kernel(const uint32_t* __restrict__ G, int c, uint32_t* __restrict__ res) {
-  __shared__ uint32_t sh[16 * kAccWords];
+  __shared__ alignas(16) uint32_t sh[16 * kAccWords];
   const int b = (int)threadIdx.x / 4;
   Fq p = b < c ? q_load(G, (uint64_t)b) : q_infinity();
 #pragma unroll 1
