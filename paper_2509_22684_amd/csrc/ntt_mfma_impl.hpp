@@ -604,7 +604,10 @@ inline bool four_per_lane(uint64_t elements) {
   return 113 * rounds4 < 100 * rounds2;
 }
 
-// Passes of multi-pass transforms (radix 2^3 .. 2^9; bridges 2^6 .. 2^9).
+// Passes of multi-pass transforms (radix 2^3 .. 2^9; bridges 2^6 .. 2^9).  A
+// bridge's launch holds one or three vectors of a plan whose first and last
+// radix agree: of radix 2^8 these are 3 x 2^16 elements or fewer (8 + 8), or
+// 2^23 and more, of radix 2^9 2^18 and more (9 + 9).
 template <class F, bool BRIDGE>
 hipError_t dispatch_multi(int log_r, const PassLaunch& a, hipStream_t s) {
   const uint64_t total = (a.grp_jobs ? a.grp_jobs : 1ull) << a.log_n;
@@ -630,12 +633,12 @@ hipError_t dispatch_multi(int log_r, const PassLaunch& a, hipStream_t s) {
         case 3: return launch_one<F, BRIDGE, 3, 9, 8>(a, s);
         case 4: return launch_one<F, BRIDGE, 4, 9, 8>(a, s);
         case 5: return launch_one<F, BRIDGE, 5, 9, 8>(a, s);
+        case 8: return launch_one<F, BRIDGE, 8, 9, 8>(a, s);
       }
     }
     switch (log_r) {
       case 6: return launch_one<F, BRIDGE, 6, 9, 8>(a, s);
       case 7: return launch_one<F, BRIDGE, 7, 9, 8>(a, s);
-      case 8: return launch_one<F, BRIDGE, 8, 9, 8>(a, s);
       case 9: return launch_one<F, BRIDGE, 9, 10, 9>(a, s);
       default: return hipErrorInvalidValue;
     }
@@ -645,13 +648,13 @@ hipError_t dispatch_multi(int log_r, const PassLaunch& a, hipStream_t s) {
       case 3: return launch_one<F, BRIDGE, 3, 8, 8>(a, s);
       case 4: return launch_one<F, BRIDGE, 4, 9, 9>(a, s);
       case 5: return launch_one<F, BRIDGE, 5, 8, 8>(a, s);
+      case 9: return launch_one<F, BRIDGE, 9, 10, 10>(a, s);
     }
   }
   switch (log_r) {
     case 6: return launch_one<F, BRIDGE, 6, 8, 8>(a, s);
     case 7: return launch_one<F, BRIDGE, 7, 9, 9>(a, s);
     case 8: return launch_one<F, BRIDGE, 8, 9, 9>(a, s);
-    case 9: return launch_one<F, BRIDGE, 9, 10, 10>(a, s);
     default: return hipErrorInvalidValue;
   }
 }
