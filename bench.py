@@ -35,8 +35,10 @@ FIELD = "bls12_381_fr"
 PEAK_MAD_PER_S = 256 * 4 * 16 * 2.4e9
 PEAK_HBM_BYTES_PER_S = 8.0e12
 MADS_PER_FFMUL = 136  # 2 s^2 + s for s = 8 limbs (one CIOS/FIPS Montgomery product)
+# what the dominant kernel is compiled from
 KERNEL_SOURCES = ["paper_2509_22684_amd/csrc/field.hpp", "paper_2509_22684_amd/csrc/mfma_tables.hpp",
-                  "paper_2509_22684_amd/csrc/ntt_mfma_impl.hpp"]
+                  "paper_2509_22684_amd/csrc/ntt_kernels.hpp", "paper_2509_22684_amd/csrc/ntt_mfma_bls.hip",
+                  "paper_2509_22684_amd/csrc/ntt_mfma_impl.hpp", "paper_2509_22684_amd/csrc/ntt_pass_impl.hpp"]
 
 
 def kernel_hash() -> str:
