@@ -172,7 +172,8 @@ def small_configs_leg(dev) -> dict:
     y = torch.empty_like(x)
     ms = med(lambda: p.forward(x, y), 50)
     out["n2e12_radix2"] = {"us_per_forward": ms * 1e3, "elements_per_s": (1 << 12) / (ms * 1e-3),
-                           "note": "launch-bound at this size; not a roofline claim"}
+                           "note": "launch-bound at this size; not a roofline claim.  The plan option asks for "
+                                   "radix-2 rounds; integer plans' rounds run on the matrix cores"}
     x = torch.from_numpy(si.uniform_field_vector(FIELD, 1 << 20, si.stream_seed(2, 0, 0)).view(np.int32)).to(dev)
     p = Plan(FIELD, 20)
     y, z = torch.empty_like(x), torch.empty_like(x)

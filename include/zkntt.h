@@ -74,13 +74,14 @@ typedef struct {
   uint32_t twiddle_mode;    /* 0 default; 1 one precomputed table per pass in HBM;
                                2 two small tables and one extra multiplication per element */
   uint32_t log2_radix;      /* radix of the in-register butterflies: 0 default (1, radix-2, up to
-                               n = 2^18; 2 above), 1 (radix-2), 2 or 3.  Read for the FP64
-                               product (2); the other passes' rounds run on the matrix cores */
+                               n = 2^18; 2 above), 1 (radix-2), 2 or 3.  Selects kernels of the
+                               FP64 product only (2); the rounds of other plans run on the matrix
+                               cores, and it only sets their default log2_tile */
   uint32_t log2_tile;       /* the largest transform run in one pass, log2: 0 default (8 for
-                               radix-2 transforms of n = 2^10 .. 2^16, else 10), 8, 10 or 11;
-                               for the FP64 product also the elements per workgroup tile of a
-                               multi-pass transform (8: register radix 2 or 4 only, passes of
-                               at most 2^7 points) */
+                               n = 2^10 .. 2^16 with log2_radix 1, else 10), 8, 10 or 11 (8 with
+                               log2_radix 3 is refused above n = 2^8); for the FP64 product also
+                               the elements per workgroup tile of a multi-pass transform (8:
+                               passes of at most 2^7 points) */
   uint32_t flags;           /* ZK_FLAG_* */
   uint32_t log2_pass_radix; /* most butterfly stages fused into one global pass: 0 default (9 up to
                                n = 2^18, so at most two passes there; 8 above), 4..9 */

@@ -11,8 +11,9 @@
 // base computed on the host, so plan creation costs milliseconds even at
 // n = 2^24.
 //
-// Transforms are sequences of Stockham passes (ntt_pass_impl.hpp, one
-// translation unit per field and register radix); the inverse runs the
+// Transforms are sequences of Stockham passes (ntt_mfma_impl.hpp on the matrix
+// cores, ntt_pass_impl.hpp in registers for short whole transforms and the
+// FP64 product; a translation unit per field); the inverse runs the
 // forward passes on the index-reversed input, since
 // sum_i X_i w^(-ij) = sum_i X_(-i mod n) w^(ij), and scales by 1/n on the
 // last pass.  Batches (ntt_batch.hip) reuse the plans' tables and pass
@@ -359,23 +360,22 @@ int resolve_opts(int field, uint32_t log2n, const ntt_plan_opts* in, ntt_plan_op
       if (!o.log2_pass_radix) o.log2_pass_radix = t.log2_pass_radix;
     }
   }
-  // Built-in defaults.  Register radix: radix-2 rounds (two elements per
-  // thread, twice the threads per tile) up to 2^18, where a transform has
-  // too few tiles to fill the chip and more waves per tile shorten each
-  // pass; radix-4 above, where every CU is busy and fewer instructions per
-  // element win.  Pass depth: up to 2^18 two passes of at most 2^9 points (a
-  // third pass would cost another launch or, in a batch, another round of
-  // tiles and dependency waits); above, passes of at most 2^8 points, which
-  // measured fastest at 2^24.
-  // Tile: 2^8 elements for radix-2 transforms of 2^10 to 2^16 points (they
-  // do not fill the chip; smaller tiles spread a pass over four times the
-  // workgroups: 2^12 in 24 us against 33 us with 2^10-element tiles), 2^10
-  // otherwise (the pass split under 2^8 tiles, passes of at most 2^7 points,
-  // would add a pass to batched jobs).
+  // Built-in defaults.  Pass depth: up to 2^18 two passes of at most 2^9 points
+  // (2^17 23.0 us in two, 24.8 in three; 2^18 34.3 and 36.3; in a batch a third
+  // pass is another round of tiles and dependency waits); above, passes of at
+  // most 2^8 points, which measured fastest at 2^24.
+  // Tile: 2^8, the largest transform in one pass, for 2^10 to 2^16 points (two
+  // passes spread over more CUs: 2^10 10.4 us, and 12.8 in one pass); 2^10
+  // otherwise, so that 2^9 points are one pass.  The matrix-core passes choose
+  // the elements per workgroup by the launch's size; only the FP64 product's
+  // kernels take them from here, and from the register radix.
+  // Register radix: 2 up to 2^18 and 4 above.  Of integer plans it selects
+  // nothing but the tile's default.
   if (!o.twiddle_mode) o.twiddle_mode = 1;
   if (!o.log2_radix) o.log2_radix = log2n <= 18 ? 1 : 2;
   if (!o.log2_tile) o.log2_tile = (log2n >= 10 && log2n <= 16 && o.log2_radix == 1) ? 8 : 10;
   if (!o.log2_pass_radix) o.log2_pass_radix = log2n <= 18 ? 9 : 8;
+  // no kernel of either product combines them; refused for every plan alike
   if (o.log2_tile == 8 && o.log2_radix == 3 && log2n > 8)
     return fail(ZK_EUNSUPPORTED, "2^8-element tiles take two or four elements per thread (log2_radix 1 or 2)");
   *out = o;
@@ -1277,8 +1277,6 @@ int batch_build(ntt_batch** out, const ntt_batch_job* specs, int njobs, bool cap
   for (int k = 0; k < njobs; ++k) total += load(k);
   // Plans with equal field, size and pass schedule hold equal tables, so a
   // group may span several such plans and run on the first one's tables.
-  // Grouped launches fill the chip, so they use radix-4 register rounds
-  // whatever the plans' register radix (the tables and bytes are the same).
   std::vector<std::vector<int>> groups;  // in order of first appearance
   {
     auto same = [&](int a, int b) {
@@ -1417,7 +1415,6 @@ int batch_build(ntt_batch** out, const ntt_batch_job* specs, int njobs, bool cap
       const ntt_batch_job& s0 = specs[g[0]];
       zk::PassLaunch a = make_pass_args(p, kinds[g[0]], q, s0.in, s0.out, s0.work);
       a.grp_jobs = (uint32_t)g.size();
-      a.log_grp_tiles = p->log_n - (uint32_t)p->passes[q].log_tile;
       d.ptr_off.push_back(ptrs.size());
       for (int k : g)
         ptrs.push_back(reinterpret_cast<uintptr_t>(make_pass_args(p, kinds[k], q, specs[k].in, specs[k].out, specs[k].work).in));

@@ -88,10 +88,11 @@ __device__ __forceinline__ uint32_t pass_tile_index(PassLaunch& a, uint32_t bloc
 }
 
 // Transforms of at most 2^kTinyLog points run in one workgroup of the
-// register kernels (ntt_pass_impl.hpp).
+// register kernels (ntt_pass_impl.hpp) in every launch; host_rules.hpp says
+// when longer ones do.
 constexpr int kTinyLog = 7;
 
-// Passes the matrix-core kernels run (ntt_mfma_impl.hpp): radix 2^3 .. 2^9
+// Passes the matrix-core kernels can run (ntt_mfma_impl.hpp): radix 2^3 .. 2^9
 // of a multi-pass transform, and whole transforms of 2^8 to 2^11 points.
 inline bool mfma_supported(int log_r, uint32_t log_n) {
   return (uint32_t)log_r == log_n ? log_r > kTinyLog && log_r <= 11 : log_n > 8 && log_r >= 3 && log_r <= 9;
@@ -118,7 +119,7 @@ hipError_t launch_field_mul(int field, int variant, const Fe* a, const Fe* b, Fe
 
 // Launch one radix-2^log_r pass.  log_tile (elements per workgroup) is used
 // by the FP64 product's kernels; the others choose their tile from the number
-// of elements in the launch and set log_grp_tiles to match.  Returns
+// of elements in the launch.  Sets log_grp_tiles to match.  Returns
 // hipSuccess or the launch error.
 hipError_t launch_pass(int field, int log_r, int log_tile, const PassLaunch& a, hipStream_t s);
 

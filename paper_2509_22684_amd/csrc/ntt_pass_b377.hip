@@ -1,4 +1,4 @@
-// Whole transforms of at most 2^7 points over BLS12-377 Fr.
+// Whole transforms in the register kernels over BLS12-377 Fr.
 #include "ntt_pass_impl.hpp"
 
 namespace zk {

@@ -1,4 +1,4 @@
-// Whole transforms of at most 2^7 points over BN254 Fr.
+// Whole transforms in the register kernels over BN254 Fr.
 #include "ntt_pass_impl.hpp"
 
 namespace zk {

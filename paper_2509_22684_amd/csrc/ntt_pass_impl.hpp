@@ -1,6 +1,7 @@
-// Register kernels: transforms of up to 2^7 points, and every pass of the FP64
-// product.  The other passes run on the matrix cores (ntt_mfma_impl.hpp), with
-// the loads, stores and products from here.
+// Register kernels: whole transforms of up to 2^7 points, of 2^8 to 2^10 in
+// launches that fill the chip, and every pass of the FP64 product.  The other
+// passes run on the matrix cores (ntt_mfma_impl.hpp), with the loads, stores
+// and products from here.
 //
 // The transform follows the paper's description of GPU NTTs (Section II-B):
 // radix-2 Cooley-Tukey butterflies, with a block of threads performing a
