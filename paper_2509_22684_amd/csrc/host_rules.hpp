@@ -67,7 +67,9 @@ inline double persistent_us(double items, double slots) { return items * kBatchI
 // without one pays for each on the host, at every launch, with a wait, a
 // record and another wait, and its launches come later (five transforms of 2^8
 // points in five launches 89 us with three, 105 with four; 64 transforms of
-// 2^10 to 2^18 points, all as launches, 413 and 501).
+// 2^10 to 2^18 points, all as launches, 413 and 501).  Not always: 16 of 2^10
+// points in twelve groups, waited for one batch at a time, 147 us with four and
+// 163 to 212 with three; one after the other 118 to 164 with three and 163.
 inline size_t side_streams(bool graph) { return graph ? 4 : 3; }
 
 }  // namespace rules
