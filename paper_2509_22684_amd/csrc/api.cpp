@@ -199,6 +199,16 @@ std::vector<int> split_passes(uint32_t log_n, const ntt_plan_opts& o) {
   const int base = (int)log_n / P, extra = (int)log_n % P;
   for (int k = 0; k < P; ++k) r.push_back(base + (k < extra ? 1 : 0));
   if (P == 3 && extra) r[0] = r[2] = base + (extra == 2), r[1] = base + (extra == 1);
+  // On the matrix cores a radix-2^5 pass is two rounds, as many as a radix-2^6
+  // one, and a radix-2^4 pass is one: four passes of 2^20 to 2^23 points are
+  // 6-4-4-6 to 6-6-5-6, bridged too, rather than 5-5-5-5 to 6-6-6-5 (quotient
+  // chains 730 against 880 us at 2^20, 1,548 and 1,715 at 2^21, 3.01 and 3.31
+  // ms at 2^22, 6.53 and 6.75 at 2^23; the register kernels took 833, 1,630,
+  // 3.33 and 6.84 with the latter).  The FP64 product's kernels keep those.
+  if (P == 4 && base == 5 && max_log_r >= 6 && !(o.flags & ZK_FLAG_FFMUL_FP64)) {
+    const int middle = (int)log_n - 12;
+    r = {6, std::min(6, middle - 4), std::max(4, middle - 6), 6};
+  }
   return r;
 }
 

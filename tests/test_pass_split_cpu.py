@@ -22,6 +22,13 @@ def table_bytes(radices):
     (11, dict(log2_tile=10), [6, 5]),
     (11, dict(log2_tile=11), [11]),
     (20, dict(log2_pass_radix=8), [7, 6, 7]),
+    (20, dict(log2_pass_radix=6), [6, 4, 4, 6]),
+    (21, dict(log2_pass_radix=6), [6, 5, 4, 6]),
+    (22, dict(log2_pass_radix=6), [6, 6, 4, 6]),
+    (22, dict(log2_pass_radix=7), [6, 6, 4, 6]),
+    (23, dict(log2_pass_radix=7), [6, 6, 5, 6]),
+    (20, dict(log2_pass_radix=5), [5, 5, 5, 5]),
+    (20, dict(log2_pass_radix=6, flags=2), [5, 5, 5, 5]),
 ])
 def test_split(log2n, opts, radices):
     _lib.ntt_tuning_clear()
